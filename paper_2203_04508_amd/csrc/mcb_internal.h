@@ -24,8 +24,9 @@ constexpr int Q3_LINKS = 20;              // 3-D: and two unused ones, so every 
 // next step: the terms of its exact-difference forcing (rho, du = F / rho, s = 2u + du and
 // duu = 1.5 du.s, from which F_j of eq. 13 follows per direction), its post-collision populations
 // 1 .. Q-1 as stored, one slot (the sum of the node's own populations on its links, which the
-// density of the next step adds: the 3-D density pass and the chemical-potential march; the 2-D
-// step of the pseudopotential model keeps population 0 as stored there, which nothing reads), and
+// density of the next step adds: the 3-D density pass, the chemical-potential march and the 2-D tiles;
+// the row march of the pseudopotential model keeps population 0 as stored there, which nothing
+// reads), and
 // the eq. 18 correction that the pull of that step applied.  The pull loads only the leading RF + Q - 1 values (a loaded value
 // that is never used frees its register while the load is in flight, and the next write to it
 // must wait for the load).
@@ -173,6 +174,9 @@ hipError_t cp_wall_mu(mcb_ctx* c);                // chemical-potential model: m
 // step2d.hip / step3d.hip: one time step from the state (fcur, rcur) to (fnext, rnext), where r are
 // the boundary records of the state (pull = false: collision of fcur in place of the pull)
 hipError_t step_fused(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull);
+// tile2d.hip: the D2Q9 step where both lattices together hold at most TILE_BYTES
+constexpr int64_t TILE_BYTES = 240000000;
+hipError_t tile2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull);
 hipError_t init_feq(mcb_ctx* c, const double* rho, const double* u, void* fout);
 
 // adjoint.hip: one transposed step (pull = 0: the first collision from f^eq(rho0, 0)), and the

@@ -174,6 +174,16 @@ __device__ __forceinline__ void node_v(const double (&j)[3], const double (&pv)[
     }
 }
 
+// |v|, each square and each sum rounded by itself (no contraction to a multiply-add), so that it is
+// bit for bit what a caller computes from the components of mcb_moments
+__device__ __forceinline__ double speed_of(const double (&v)[3], int dim) {
+#pragma clang fp contract(off)
+    double s2 = v[0] * v[0];
+    s2 = s2 + v[1] * v[1];
+    if (dim > 2) s2 = s2 + v[2] * v[2];
+    return sqrt(s2);
+}
+
 // ---- moments: rho, psi (fluid and wall nodes), then v = (j - F / 2) / rho.  Q is a template
 // parameter (unrolled direction loops); each lane loads all it needs before using any.
 // k_rho_out: the density alone (the chemical-potential model's velocity needs no psi)
@@ -295,9 +305,7 @@ __global__ __launch_bounds__(256) void k_vel_out(GridDev g, const S* __restrict_
         const double gk[3] = {gx, gy, gz};
         node_v<Q>(j, pv, psi[x], rho[x], G, gk, g.dim, vv);
         if (SPEED) {
-            double s2 = 0.0;
-            for (int k = 0; k < g.dim; ++k) s2 += vv[k] * vv[k];
-            speed_pick(best, at, fl ? sqrt(s2) : -1.0, fl ? double(x) : -1.0);
+            speed_pick(best, at, fl ? speed_of(vv, g.dim) : -1.0, fl ? double(x) : -1.0);
         } else {
             for (int k = 0; k < g.dim; ++k) v[k * g.N + x] = fl ? vv[k] : 0.0;
         }
@@ -343,10 +351,8 @@ __global__ __launch_bounds__(256) void k_vel_cp(GridDev g, const S* __restrict__
                           d1(at(fr, 0, -2), at(fr, 0, -1), at(fr, 0, 1), at(fr, 0, 2)) / 3.0 + r * gy;
         const double vx = (jx - 0.5 * Fx) / rx, vy = (jy - 0.5 * Fy) / rx;
         if (SPEED) {
-            double s2 = 0.0;
-            s2 += vx * vx;
-            s2 += vy * vy;
-            speed_pick(vbest, vat, fl ? sqrt(s2) : -1.0, fl ? double(x) : -1.0);
+            const double vv[3] = {vx, vy, 0.0};
+            speed_pick(vbest, vat, fl ? speed_of(vv, 2) : -1.0, fl ? double(x) : -1.0);
         } else {
             v[x] = fl ? vx : 0.0;
             v[g.N + x] = fl ? vy : 0.0;
@@ -554,8 +560,7 @@ __global__ __launch_bounds__(SW) void k_speed2d(GridDev g, const S* __restrict__
                 }
                 double v[3];
                 node_v<9>(jA[h], pv, s_psi[p0][c], rA[h], G, gk, 2, v);
-                const double sp = sqrt(v[0] * v[0] + v[1] * v[1]);
-                speed_pick(best, at, sp, double(int64_t(rowof(k - 2)) * g.nx + xc[h]));
+                speed_pick(best, at, speed_of(v, 2), double(int64_t(rowof(k - 2)) * g.nx + xc[h]));
             }
         }
     }

@@ -20,7 +20,7 @@
 // buffers with the lattice buffers, since halo lanes of neighbouring workgroups read a node's
 // record of time t while its owner writes that of t+1.
 //
-// Layout: a workgroup of W lanes (one or four waves) covers W consecutive columns -- W - 4 output
+// Layout: a workgroup of W lanes (four waves) covers W consecutive columns -- W - 4 output
 // columns and two halo columns on each side -- over a segment of H rows, and marches up the
 // segment one row per iteration.  Each iteration
 //   A  reduces the populations pulled for the current row to rho and puts rho and the node tag
@@ -38,39 +38,10 @@
 // (no load or store sits in a divergent branch, so the wait counters stay exact), and the lane
 // part of a pull address is loop-invariant, the row part a wave-uniform scalar: each vector
 // memory instruction moves a full row of one population with no address arithmetic.
-#include "kernels_common.h"
+#include "step2d_node.h"
 
 namespace mcb {
 namespace {
-
-template <class S, class C>
-struct Args2 {
-    const S* fa;                 // post-collision populations of time t, SoA [9][N]
-    S* fb;                       // post-collision populations of time t+1
-    const int32_t* tag;          // >0: (boundary index << 8) | link bits; 0 fluid; -1 solid; -2-w wall w
-    const C* rin;                // boundary records of time t, REC2 per boundary node
-    C* rout;                     // boundary records of time t+1
-    const C* la;                 // link coefficients, Q2_LINKS per boundary node (NO_LINK: none)
-    const C* fac;                // eq. 15 factor per wall node: phi / weight of its fluid neighbours
-    int32_t* flags;
-    uint32_t n_bnodes, n_wall;
-    int nx, ny, H, nsx, nblocks;
-    C tau_inv, G, rho_ref;
-    C kF, k18;                   // boundary scheme: weight of the forcing term, of eq. 18 (0 or 1)
-    C s_e, s_eps, s_q;           // rates of the multiple-relaxation-time collision (eq. 3)
-    C gx, gy;                    // body acceleration: F = F_nonideal + rho g, so du = F / rho gains g
-    Eos<C> eos;
-};
-
-// D2Q9 weights
-template <class C>
-__device__ inline C w9(int i) {
-    return i == 0 ? C(4.0 / 9.0) : (i < 5 ? C(1.0 / 9.0) : C(1.0 / 36.0));
-}
-
-__device__ constexpr int kOpp[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
-__device__ constexpr int kEx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
-__device__ constexpr int kEy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 
 // Per-workgroup state of the row march.
 template <class S, class C, int W>
@@ -118,133 +89,6 @@ __device__ __forceinline__ void pull_row(const March<S, C, W>& M, int r, bool on
         const uint32_t so = uint32_t(i + (kMixed<S> ? 1 : 0)) * M.ns + (PULL ? rowof[kEy[i] + 1] : r0);
         f[i] = Buf<S>::ld(M.fa, vo, so);
     }
-}
-
-// e.(x, y) for a lattice vector of components 0 and +-1, folded when the components are constants
-// (a product with 0 cannot be dropped under IEEE rules)
-template <class C>
-__device__ __forceinline__ C edot(int ex, int ey, C x, C y) {
-    const C tx = ex > 0 ? x : -x, ty = ey > 0 ? y : -y;
-    return ex == 0 ? ty : (ey == 0 ? tx : tx + ty);
-}
-
-// Eqs. 16-18 at a boundary node (bnd) from its record of time t (rec) and link coefficients (ca):
-// replaces the populations pulled from solid neighbours by f_in and corrects the rest population;
-// returns the correction and, in res, what rounding f_0 + correction to the compute type dropped.
-// Lanes that are not boundary nodes keep f and return zeros.  Directions in which no lane of the wave has a link are
-// skipped.  kF and k18 select the scheme: 1 and 1 the present one, 0 and 0 linear interpolation
-// bounce-back (no forcing term, no eq. 18), 0 and 1 the same with eq. 18; halfway bounce-back is
-// a = 1 on every link.
-template <class S, class C>
-__device__ __forceinline__ C apply_links(bool bnd, const C (&rec)[RF2 + 8], const C (&ca)[Q2_LINKS], C (&f)[9], C kF,
-                                         C k18, C& res) {
-    const C rho = rec[0] * kF, dux = rec[1], duy = rec[2], sx = rec[3], sy = rec[4], duu = rec[5];
-    const C* fo = rec + RF2 - 1;  // own post-collision populations 1 .. 8
-    // each slot opp(j) is replaced at most once, and never one that a later eq. 16 link reads (its
-    // x2 = x - e_j is fluid, while a replaced slot was pulled from a solid node)
-    double ds = 0.0;
-#pragma unroll
-    for (int j = 1; j < 9; ++j) {
-        const C a = ca[j - 1];
-        const bool lk = bnd && a < C(1.5);
-        if (__builtin_amdgcn_ballot_w64(lk)) {
-            const C c1 = a < C(0) ? -a : a, c2 = C(1) - c1;
-            // eq. 13 term of direction j: w rho [3 e.du + 4.5 (e.du)(e.s) - 1.5 du.s]
-            const C ed = edot<C>(kEx[j], kEy[j], dux, duy);
-            const C es = edot<C>(kEx[j], kEy[j], sx, sy);
-            const C Fj = w9<C>(j) * rho * (C(3) * ed + C(4.5) * ed * es - duu);
-            C o = a < C(0) ? fo[kOpp[j]] : f[j];
-            o = c2 != C(0) ? o : C(0);
-            // rounded to the storage format, as the value would be stored; eq. 18 takes it so
-            const C fin = Buf<S>::round(c1 * fo[j] + c2 * (o + Fj));
-            ds += lk ? double(fo[j]) - double(fin) : 0.0;
-            f[kOpp[j]] = lk ? fin : f[kOpp[j]];
-        }
-    }
-    ds *= double(k18);
-    const double f0 = double(f[0]) + ds;
-    f[0] = C(f0);
-    res = C(f0 - double(f[0]));
-    return C(ds);
-}
-
-// Collision of one node (eq. 4, or eqs. 1-4 when MRT; eq. 13 forcing, eq. 14 equilibrium) from its
-// pulled populations fA (stored format: shifted by w_i rho_ref), their sum rs_acc and the force
-// (Fx, Fy) without the body force.  Writes the post-collision populations rounded to the storage
-// format, f_0 taking the rounding so that the node keeps its mass exactly, and the forcing terms
-// the boundary record carries.  coll = false (lanes that collide nothing) keeps the arithmetic finite.
-template <class S, class C, bool MRT>
-__device__ __forceinline__ void collide9(const Args2<S, C>& a, bool coll, const C (&fA)[9], MassAcc<S, C> rs_acc, C Fx, C Fy,
-                                         C (&out)[9], C& rho, C& dux, C& duy, C& sx2, C& sy2, C& duu15) {
-    const C rs = C(rs_acc);
-    rho = rs + a.rho_ref;
-    const C irho = rcp(coll ? rho : C(1));
-    const C jx = fA[1] - fA[3] + fA[5] - fA[6] - fA[7] + fA[8];
-    const C jy = fA[2] - fA[4] + fA[5] + fA[6] - fA[7] - fA[8];
-    const C ux = jx * irho, uy = jy * irho;
-    dux = Fx * irho + a.gx;
-    duy = Fy * irho + a.gy;
-    const C ti = a.tau_inv, omc = C(1) - ti;
-    // per direction: out_i = f_i (1 - 1/tau) + w_i [rs/tau + rho (sym_i +- anti_i)] with
-    //   sym  = (4.5 (e.u)^2 - 1.5 u^2) / tau + 4.5 (e.du)(e.(2u + du)) - 1.5 du.(2u + du)
-    //   anti = 3 (e.u / tau + e.du)
-    // (eq. 14 equilibrium, eq. 13 forcing term, eq. 4 with S = I / tau)
-    const C uu15 = C(1.5) * (ux * ux + uy * uy);
-    sx2 = C(2) * ux + dux;
-    sy2 = C(2) * uy + duy;
-    duu15 = C(1.5) * (dux * sx2 + duy * sy2);
-    const C c0 = -(ti * uu15 + duu15);
-    const C trs = ti * rs;
-    auto pair = [&](int ip, int im, C w, C eu, C ed, C es) {
-        const C sym = ti * C(4.5) * eu * eu + C(4.5) * ed * es + c0;
-        const C anti = C(3) * (ti * eu + ed);
-        const C base = w * (trs + rho * sym);
-        const C wra = w * rho * anti;
-        out[ip] = fA[ip] * omc + base + wra;
-        out[im] = fA[im] * omc + base - wra;
-    };
-    if constexpr (!MRT) {
-        pair(1, 3, C(1.0 / 9.0), ux, dux, sx2);
-        pair(2, 4, C(1.0 / 9.0), uy, duy, sy2);
-        pair(5, 7, C(1.0 / 36.0), ux + uy, dux + duy, sx2 + sy2);
-        pair(6, 8, C(1.0 / 36.0), uy - ux, duy - dux, sy2 - sx2);
-    } else {
-        // eqs. 1-4 with the moment matrix of eq. 2: the six non-conserved moments of the stored
-        // populations (the shift w_i rho_ref has moments rho_ref, -2 rho_ref, rho_ref, 0, ...,
-        // folded in through rs), relaxed at the eq. 3 rates toward the Sec. 2.1 equilibria
-        // (q^eq = -j); M^-1 = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4)
-        const C s14 = fA[1] + fA[2] + fA[3] + fA[4], s58 = fA[5] + fA[6] + fA[7] + fA[8];
-        const C jj = rho * (ux * ux + uy * uy);
-        const C de = a.s_e * (C(-4) * fA[0] - s14 + C(2) * s58 + C(2) * rs - C(3) * jj) * C(1.0 / 36.0);
-        const C dp = a.s_eps * (C(4) * fA[0] - C(2) * s14 + s58 - rs + C(3) * jj) * C(1.0 / 36.0);
-        const C dx = a.s_q * (C(-2) * (fA[1] - fA[3]) + (fA[5] - fA[6] - fA[7] + fA[8]) + jx) * C(1.0 / 12.0);
-        const C dy = a.s_q * (C(-2) * (fA[2] - fA[4]) + (fA[5] + fA[6] - fA[7] - fA[8]) + jy) * C(1.0 / 12.0);
-        const C dxx = ti * (fA[1] - fA[2] + fA[3] - fA[4] - rho * (ux * ux - uy * uy)) * C(0.25);
-        const C dxy = ti * (fA[5] - fA[6] + fA[7] - fA[8] - rho * ux * uy) * C(0.25);
-        // out = f - M^-1 S (m - m_eq) + F_i, F_i the eq. 13 term, by opposite pairs
-        auto mpair = [&](int ip, int im, C w, C ed, C es, C sym, C anti) {
-            const C wr = w * rho;
-            const C fs = wr * (C(4.5) * ed * es - duu15) + sym;
-            const C fa = wr * C(3) * ed + anti;
-            out[ip] = fA[ip] + fs + fa;
-            out[im] = fA[im] + fs - fa;
-        };
-        const C e1 = de + C(2) * dp, e2 = C(2) * de + dp;
-        mpair(1, 3, C(1.0 / 9.0), dux, sx2, e1 - dxx, C(2) * dx);
-        mpair(2, 4, C(1.0 / 9.0), duy, sy2, e1 + dxx, C(2) * dy);
-        mpair(5, 7, C(1.0 / 36.0), dux + duy, sx2 + sy2, -(e2 + dxy), -(dx + dy));
-        mpair(6, 8, C(1.0 / 36.0), duy - dux, sy2 - sx2, -(e2 - dxy), -(dy - dx));
-    }
-    // collision conserves mass (the equilibrium and the forcing term of eq. 13 have zero net
-    // mass): set f_0 to the density minus the other eight outputs as stored, so the rounding of
-    // the lattice weights and of the storage format cannot bias the total mass
-    MassAcc<S, C> rest = 0;
-#pragma unroll
-    for (int i = 1; i < 9; ++i) {
-        out[i] = Buf<S>::round(out[i]);
-        rest += MassAcc<S, C>(out[i]);
-    }
-    out[0] = C(rs_acc - rest);
 }
 
 // One row of the march (iteration k, row r = y0 - 2 + k).  fC holds the pulled populations of row
@@ -486,58 +330,24 @@ __global__ __launch_bounds__(W) void k_step2d(Args2<S, C> a) {
 template <class S, class C, int W, int OUT>
 hipError_t launch_w(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
     const bool mrt = c->p.collision == MCB_COLL_MRT;
-    Args2<S, C> a;
-    a.fa = static_cast<const S*>(fcur);
-    a.fb = static_cast<S*>(fnext);
-    a.tag = reinterpret_cast<const int32_t*>(c->lat + c->L.tag);
-    a.rin = static_cast<const C*>(rcur);
-    a.rout = static_cast<C*>(rnext);
-    a.la = reinterpret_cast<const C*>(c->lk + c->L.lk_a);
-    a.fac = reinterpret_cast<const C*>(c->lk + c->L.wl_fac);
-    a.flags = reinterpret_cast<int32_t*>(c->lat + c->L.flags);
-    a.n_bnodes = uint32_t(c->n_bnodes > 0 ? c->n_bnodes : 0);
-    a.n_wall = uint32_t(c->n_wall > 0 ? c->n_wall : 0);
-    a.nx = c->p.nx;
-    a.ny = c->p.ny;
+    Args2<S, C> a = step_args<S, C>(c, fcur, rcur, fnext, rnext);
     a.nsx = (a.nx + OUT - 1) / OUT;
-    // segment height: long segments amortise the four halo rows; short ones fill the chip.  Wide
-    // strips: as many segments as the device holds in a number of resident rounds -- four with
+    // segment height: as many segments as the device holds in a number of resident rounds -- four with
     // FP32 storage (the shorter segments' extra halo rows cost less than the march loses when every
     // workgroup moves in step with the others), one with FP16 storage, whose arithmetic is the limit
-    // and grows with the halo rows, and with FP64; one-wave strips (small lattices): enough
-    // workgroups to fill the chip several times over.
-    int H;
-    if (W == 64) {
-        H = 64;
-        while (H > 8 && int64_t(a.nsx) * ((a.ny + H - 1) / H) < 8192) H >>= 1;
-    } else {
-        // a context runs one storage type and one strip width, so four slots cover its variants
-        int* occ = c->occ;
-        const int cap = pull ? (mrt ? resident_blocks(c, k_step2d<S, C, W, OUT, true, true>, W, &occ[3])
-                                    : resident_blocks(c, k_step2d<S, C, W, OUT, true, false>, W, &occ[1]))
-                             : (mrt ? resident_blocks(c, k_step2d<S, C, W, OUT, false, true>, W, &occ[2])
-                                    : resident_blocks(c, k_step2d<S, C, W, OUT, false, false>, W, &occ[0]));
-        const int rounds = sizeof(S) == 4 ? 4 : 1;
-        const int per = rounds * cap / a.nsx > 0 ? rounds * cap / a.nsx : 1;  // segments per strip
-        H = (a.ny + per - 1) / per;
-        if (H < 16) H = 16;
-    }
+    // and grows with the halo rows, and with FP64.  A context runs one storage type, so four slots
+    // cover its variants.
+    int* occ = c->occ;
+    const int cap = pull ? (mrt ? resident_blocks(c, k_step2d<S, C, W, OUT, true, true>, W, &occ[3])
+                                : resident_blocks(c, k_step2d<S, C, W, OUT, true, false>, W, &occ[1]))
+                         : (mrt ? resident_blocks(c, k_step2d<S, C, W, OUT, false, true>, W, &occ[2])
+                                : resident_blocks(c, k_step2d<S, C, W, OUT, false, false>, W, &occ[0]));
+    const int rounds = sizeof(S) == 4 ? 4 : 1;
+    const int per = rounds * cap / a.nsx > 0 ? rounds * cap / a.nsx : 1;  // segments per strip
+    int H = (a.ny + per - 1) / per;
+    if (H < 16) H = 16;
     a.H = H;
     a.nblocks = a.nsx * ((a.ny + H - 1) / H);
-    a.tau_inv = C(1.0 / c->p.tau);
-    a.G = C(c->p.G);
-    a.rho_ref = c->p.precision == MCB_F64 ? C(0) : C(c->p.rho_ref);
-    a.kF = c->p.bc_mode == MCB_BC_PRESENT ? C(1) : C(0);
-    a.k18 = c->p.bc_mode == MCB_BC_IBC ? C(0) : C(1);
-    a.s_e = C(c->p.s_e);
-    a.s_eps = C(c->p.s_eps);
-    a.s_q = C(c->p.s_q);
-    a.gx = C(c->p.gravity[0]);
-    a.gy = C(c->p.gravity[1]);
-    a.eos.RT = C(c->p.eos_R * c->p.eos_T);
-    a.eos.a = C(c->p.eos_a);
-    a.eos.b4 = C(c->p.eos_b / 4.0);
-    a.eos.two_over_G = C(2.0 / c->p.G);
     if (pull && !mrt)
         hipLaunchKernelGGL((k_step2d<S, C, W, OUT, true, false>), dim3(a.nblocks), dim3(W), 0, c->stream, a);
     else if (pull)
@@ -551,10 +361,8 @@ hipError_t launch_w(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext,
 
 template <class S, class C>
 hipError_t launch_step2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
-    // one-wave strips keep small lattices busy; on large lattices the strips are a whole number of
-    // cache lines wide (224 FP32 / FP64 columns, 192 FP16 columns), so that no line is shared
-    // between strips or written in parts
-    if (c->g.N <= (int64_t(1) << 21)) return launch_w<S, C, 64, 60>(c, fcur, rcur, fnext, rnext, pull);
+    // strips a whole number of cache lines wide (224 FP32 / FP64 columns, 192 FP16 columns), so that
+    // no line is shared between strips or written in parts
     if (sizeof(S) == 2) return launch_w<S, C, 256, 192>(c, fcur, rcur, fnext, rnext, pull);
     return launch_w<S, C, 256, 224>(c, fcur, rcur, fnext, rnext, pull);
 }
@@ -566,17 +374,6 @@ hipError_t launch_step2d(mcb_ctx* c, const void* fcur, const void* rcur, void* f
 // The pass kernels that follow compute the same fields over the whole lattice, one stage each
 // (density with eqs. 16-18, the two solid layers of eq. 15, the chemical potential of eq. 12), for
 // the velocity output, which needs them at every node.
-template <class S, class C>
-struct ArgsCP {
-    Args2<S, C> a;
-    C* rho;                 // density of the step: fluid nodes and solid layers 1-2
-    C* mu;                  // chemical potential of the step: fluid nodes and solid layers 1-2
-    const int8_t* layer;    // 0 fluid, 1 wall node, 2 second solid layer, 3 deeper
-    const double* mus;      // assigned chemical potential per wall node
-    C k2, kappa;            // eq. 12: k^2 and kappa
-    C RT, b, c_log, aal;    // eq. 11: R T, b, a alpha / (2 sqrt 2 b), a alpha
-};
-
 // the populations pulled into node (cx, cy) (PULL; otherwise its own stored ones)
 template <class S, class C, bool PULL>
 __device__ __forceinline__ void pull_pops(const Args2<S, C>& a, int64_t N, int cx, int cy, C (&f)[9]) {
@@ -688,23 +485,8 @@ __global__ __launch_bounds__(256) void k_cp_layer(ArgsCP<S, C> p, const int32_t*
     }
 }
 
-// fourth-order central differences along an axis from the values at offsets -2 .. +2
-template <class C>
-__device__ __forceinline__ C cd1(C m2, C m1, C p1, C p2) {
-    return (C(8) * (p1 - m1) - (p2 - m2)) * C(1.0 / 12.0);
-}
-template <class C>
-__device__ __forceinline__ C cd2(C m2, C m1, C c, C p1, C p2) {
-    return (C(16) * (p1 + m1) - (p2 + m2) - C(30) * c) * C(1.0 / 12.0);
-}
-
 // rows of one lane in the chemical-potential pass
 constexpr int CP_MU_ROWS = 4;
-
-__device__ __forceinline__ int wrapm(int v, int n) {
-    const int r = v % n;
-    return r < 0 ? r + n : r;
-}
 
 // chemical potential on the fluid nodes: eq. 12 with the Peng-Robinson mu of eq. 11 (the solid
 // layers' values depend on the assigned ones alone and are written when those are set:
@@ -1090,52 +872,6 @@ inline unsigned cp_grid(int64_t n) {
 }
 
 
-// the arguments of the chemical-potential kernels for one step from fcur / rcur to fnext / rnext
-template <class S, class C>
-ArgsCP<S, C> cp_args(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext) {
-    ArgsCP<S, C> p;
-    Args2<S, C>& a = p.a;
-    a.fa = static_cast<const S*>(fcur);
-    a.fb = static_cast<S*>(fnext);
-    a.tag = reinterpret_cast<const int32_t*>(c->lat + c->L.tag);
-    a.rin = static_cast<const C*>(rcur);
-    a.rout = static_cast<C*>(rnext);
-    a.la = reinterpret_cast<const C*>(c->lk + c->L.lk_a);
-    a.fac = nullptr;
-    a.flags = reinterpret_cast<int32_t*>(c->lat + c->L.flags);
-    a.n_bnodes = uint32_t(c->n_bnodes > 0 ? c->n_bnodes : 0);
-    a.n_wall = uint32_t(c->n_wall > 0 ? c->n_wall : 0);
-    a.nx = c->p.nx;
-    a.ny = c->p.ny;
-    a.H = a.nsx = a.nblocks = 0;
-    a.tau_inv = C(1.0 / c->p.tau);
-    a.G = C(0);
-    a.rho_ref = c->p.precision == MCB_F64 ? C(0) : C(c->p.rho_ref);
-    a.kF = c->p.bc_mode == MCB_BC_PRESENT ? C(1) : C(0);
-    a.k18 = c->p.bc_mode == MCB_BC_IBC ? C(0) : C(1);
-    a.s_e = C(c->p.s_e);
-    a.s_eps = C(c->p.s_eps);
-    a.s_q = C(c->p.s_q);
-    a.gx = C(c->p.gravity[0]);
-    a.gy = C(c->p.gravity[1]);
-    a.eos = Eos<C>{};
-    p.rho = reinterpret_cast<C*>(c->lat + c->L.cp_rho);
-    p.mu = reinterpret_cast<C*>(c->lat + c->L.cp_mu);
-    p.layer = reinterpret_cast<const int8_t*>(c->lat + c->L.cp_layer);
-    p.mus = reinterpret_cast<const double*>(c->lk + c->L.wl_phi);
-    const double T = c->p.eos_T, Tc = pr_tc(c->p.eos_a, c->p.eos_b, c->p.eos_R);
-    const double om = c->p.pr_omega, mm = 0.37464 + 1.54226 * om - 0.26992 * om * om;
-    const double sa = 1.0 + mm * (1.0 - std::sqrt(T / Tc));
-    const double aal = c->p.eos_a * sa * sa;
-    p.k2 = C(c->p.cp_k * c->p.cp_k);
-    p.kappa = C(c->p.cp_kappa);
-    p.RT = C(c->p.eos_R * T);
-    p.b = C(c->p.eos_b);
-    p.c_log = C(aal / (2.0 * std::sqrt(2.0) * c->p.eos_b));
-    p.aal = C(aal);
-    return p;
-}
-
 // The density and chemical-potential fields of a collision from the populations fpre (pulled with
 // eqs. 16-18 from the records rpre when pull) into the context's field buffers: the pass kernels.
 // The march keeps the fields in LDS; the velocity output asks for them through cp_fields.
@@ -1228,6 +964,13 @@ hipError_t step2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, v
             default: return launch_cp<__half, float>(c, fcur, rcur, fnext, rnext, pull);
         }
     }
+    // The tile kernels re-read a ring around every tile, the march a few halo rows and columns: where
+    // the two lattices stay in the 256 MB memory-side cache the ring costs little and the tiles' shorter
+    // chains win (FP32 1800 x 1500, 194 MB: 45 us against 77; FP16 2000 x 1850, 148 MB: 50 against 77;
+    // FP64 1531 x 1021, 225 MB: 49 against 81); past it the march does (FP32 2000 x 1850, 266 MB: 94
+    // against 111; FP16 2560 x 2500, 256 MB: 116 against 127; FP64 1400 x 1300, 262 MB: 88 against 84,
+    // 1800 x 1500, 389 MB: the same 125).
+    if (2 * state_bytes(c->p.precision, 9, c->g.N) <= TILE_BYTES) return tile2d(c, fcur, rcur, fnext, rnext, pull);
     switch (c->p.precision) {
         case MCB_F64: return launch_step2d<double, double>(c, fcur, rcur, fnext, rnext, pull);
         case MCB_F32S: return launch_step2d<float, float>(c, fcur, rcur, fnext, rnext, pull);

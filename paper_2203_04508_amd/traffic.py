@@ -32,7 +32,7 @@ def kernel_digest(dim: int) -> str:
     """Hash of the sources the step kernel of a dimension is built from: counters taken on another
     version of the kernel do not describe this one."""
     h = hashlib.sha256()
-    for f in ("step2d.hip" if dim == 2 else "step3d.hip", "kernels_common.h", "mcb_internal.h"):
+    for f in (*(("step2d.hip", "step2d_node.h") if dim == 2 else ("step3d.hip",)), "kernels_common.h", "mcb_internal.h"):
         h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()[:16]
 
