@@ -24,7 +24,7 @@ constexpr int Q3_LINKS = 20;              // 3-D: and two unused ones, so every 
 // next step: the terms of its exact-difference forcing (rho, du = F / rho, s = 2u + du and
 // duu = 1.5 du.s, from which F_j of eq. 13 follows per direction), its post-collision populations
 // 1 .. Q-1 as stored, one slot (the sum of the node's own populations on its links, which the
-// density of the next step adds: the 3-D density pass, the chemical-potential march and the 2-D tiles;
+// density of the next step adds: the 3-D density pass and the 2-D tiles;
 // the row march of the pseudopotential model keeps population 0 as stored there, which nothing
 // reads), and
 // the eq. 18 correction that the pull of that step applied.  The pull loads only the leading RF + Q - 1 values (a loaded value

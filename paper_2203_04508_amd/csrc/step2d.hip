@@ -20,7 +20,7 @@
 // buffers with the lattice buffers, since halo lanes of neighbouring workgroups read a node's
 // record of time t while its owner writes that of t+1.
 //
-// Layout: a workgroup of W lanes (four waves) covers W consecutive columns -- W - 4 output
+// Layout: a workgroup of W lanes (one or four waves) covers W consecutive columns -- W - 4 output
 // columns and two halo columns on each side -- over a segment of H rows, and marches up the
 // segment one row per iteration.  Each iteration
 //   A  reduces the populations pulled for the current row to rho and puts rho and the node tag
@@ -332,20 +332,27 @@ hipError_t launch_w(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext,
     const bool mrt = c->p.collision == MCB_COLL_MRT;
     Args2<S, C> a = step_args<S, C>(c, fcur, rcur, fnext, rnext);
     a.nsx = (a.nx + OUT - 1) / OUT;
-    // segment height: as many segments as the device holds in a number of resident rounds -- four with
-    // FP32 storage (the shorter segments' extra halo rows cost less than the march loses when every
-    // workgroup moves in step with the others), one with FP16 storage, whose arithmetic is the limit
-    // and grows with the halo rows, and with FP64.  A context runs one storage type, so four slots
-    // cover its variants.
-    int* occ = c->occ;
-    const int cap = pull ? (mrt ? resident_blocks(c, k_step2d<S, C, W, OUT, true, true>, W, &occ[3])
-                                : resident_blocks(c, k_step2d<S, C, W, OUT, true, false>, W, &occ[1]))
-                         : (mrt ? resident_blocks(c, k_step2d<S, C, W, OUT, false, true>, W, &occ[2])
-                                : resident_blocks(c, k_step2d<S, C, W, OUT, false, false>, W, &occ[0]));
-    const int rounds = sizeof(S) == 4 ? 4 : 1;
-    const int per = rounds * cap / a.nsx > 0 ? rounds * cap / a.nsx : 1;  // segments per strip
-    int H = (a.ny + per - 1) / per;
-    if (H < 16) H = 16;
+    // segment height.  Wide strips: as many segments as the device holds in a number of resident
+    // rounds -- four with FP32 storage (the shorter segments' extra halo rows cost less than the march
+    // loses when every workgroup moves in step with the others), one with FP16 storage, whose
+    // arithmetic is the limit and grows with the halo rows, and with FP64; one-wave strips (small
+    // lattices): enough workgroups to fill the chip several times over.
+    int H;
+    if (W == 64) {
+        H = 64;
+        while (H > 8 && int64_t(a.nsx) * ((a.ny + H - 1) / H) < 8192) H >>= 1;
+    } else {
+        // a context runs one storage type, so four slots cover its variants
+        int* occ = c->occ;
+        const int cap = pull ? (mrt ? resident_blocks(c, k_step2d<S, C, W, OUT, true, true>, W, &occ[3])
+                                    : resident_blocks(c, k_step2d<S, C, W, OUT, true, false>, W, &occ[1]))
+                             : (mrt ? resident_blocks(c, k_step2d<S, C, W, OUT, false, true>, W, &occ[2])
+                                    : resident_blocks(c, k_step2d<S, C, W, OUT, false, false>, W, &occ[0]));
+        const int rounds = sizeof(S) == 4 ? 4 : 1;
+        const int per = rounds * cap / a.nsx > 0 ? rounds * cap / a.nsx : 1;  // segments per strip
+        H = (a.ny + per - 1) / per;
+        if (H < 16) H = 16;
+    }
     a.H = H;
     a.nblocks = a.nsx * ((a.ny + H - 1) / H);
     if (pull && !mrt)
@@ -362,7 +369,10 @@ hipError_t launch_w(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext,
 template <class S, class C>
 hipError_t launch_step2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
     // strips a whole number of cache lines wide (224 FP32 / FP64 columns, 192 FP16 columns), so that
-    // no line is shared between strips or written in parts
+    // no line is shared between strips or written in parts; small boxes (FP16 storage alone comes
+    // here with them) take one-wave strips, which keep more workgroups busy
+    if constexpr (sizeof(S) == 2)
+        if (c->g.N <= (int64_t(1) << 21)) return launch_w<S, C, 64, 60>(c, fcur, rcur, fnext, rnext, pull);
     if (sizeof(S) == 2) return launch_w<S, C, 256, 192>(c, fcur, rcur, fnext, rnext, pull);
     return launch_w<S, C, 256, 224>(c, fcur, rcur, fnext, rnext, pull);
 }
@@ -370,20 +380,10 @@ hipError_t launch_step2d(mcb_ctx* c, const void* fcur, const void* rcur, void* f
 // ---------------------------------------------------------------- chemical-potential model (2-D)
 // The paper's multiphase model (Secs. 2.2-2.3): the force needs the density and the chemical
 // potential two nodes away on each axis, and the chemical potential itself the density two nodes
-// away.  A step runs as one march (k_cp_march below) that keeps the fields of a few rows in LDS.
-// The pass kernels that follow compute the same fields over the whole lattice, one stage each
-// (density with eqs. 16-18, the two solid layers of eq. 15, the chemical potential of eq. 12), for
-// the velocity output, which needs them at every node.
-// the populations pulled into node (cx, cy) (PULL; otherwise its own stored ones)
-template <class S, class C, bool PULL>
-__device__ __forceinline__ void pull_pops(const Args2<S, C>& a, int64_t N, int cx, int cy, C (&f)[9]) {
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        const int sx = PULL ? wrap1(cx - kEx[i], a.nx) : cx, sy = PULL ? wrap1(cy - kEy[i], a.ny) : cy;
-        f[i] = ldp<S, C>(a.fa, i, N, int64_t(sy) * a.nx + sx);
-    }
-}
-
+// away.  A step runs in the tile kernels (tile2d.hip), which keep the fields of a tile in LDS, or with
+// FP16 storage as one march (k_cp_march below), which keeps those of a few rows there.  The pass kernels that follow compute the same fields over the whole lattice, one stage each (density
+// with eqs. 16-18, the two solid layers of eq. 15, the chemical potential of eq. 12), for the velocity
+// output, which needs them at every node.
 // eqs. 16-18 on pulled populations f of a node with tag tg; ds = the eq. 18 correction
 template <class S, class C, bool PULL>
 __device__ __forceinline__ void pull_links(const Args2<S, C>& a, int tg, C (&f)[9], C& ds, C& res) {
@@ -600,10 +600,9 @@ __global__ __launch_bounds__(256) void k_cp_mu_solid(int nx, int ny, const int8_
 // oldest).  25.5 KB of LDS per 256-lane workgroup in FP32, so the VGPRs decide the occupancy.
 constexpr int CP_RING = 10, CP_TRING = 8, CP_MRING = 5;
 
-// Waves per SIMD: FP32 arithmetic with MRT fits 96 VGPRs without spilling, five waves (BGK would
-// spill); FP64 fits 168 with a 20-28 byte spill, three waves instead of two (measured faster)
+// Waves per SIMD: FP32 arithmetic with MRT fits 96 VGPRs without spilling, five waves (BGK would spill)
 template <class S, class C, int W, int OUT, bool PULL, bool MRT>
-__global__ __launch_bounds__(W, (sizeof(C) == 4 && MRT) ? 5 : (sizeof(C) == 8 ? 3 : 2)) void k_cp_march(ArgsCP<S, C> p) {
+__global__ __launch_bounds__(W, MRT ? 5 : 2) void k_cp_march(ArgsCP<S, C> p) {
     constexpr int HC = (W - OUT) / 2;
     static_assert(HC >= 6, "six halo columns on either side");
     constexpr uint32_t s = sizeof(S), sc = sizeof(C), P0 = kMixed<S> ? 1 : 0;
@@ -874,7 +873,7 @@ inline unsigned cp_grid(int64_t n) {
 
 // The density and chemical-potential fields of a collision from the populations fpre (pulled with
 // eqs. 16-18 from the records rpre when pull) into the context's field buffers: the pass kernels.
-// The march keeps the fields in LDS; the velocity output asks for them through cp_fields.
+// The step keeps the fields in LDS; the velocity output asks for them through cp_fields.
 template <class S, class C>
 hipError_t cp_fields_t(mcb_ctx* c, const void* fpre, const void* rpre, bool pull) {
     ArgsCP<S, C> p = cp_args<S, C>(c, fpre, rpre, nullptr, nullptr);
@@ -922,13 +921,11 @@ hipError_t launch_cp_w(mcb_ctx* c, const void* fcur, const void* rcur, void* fne
     return hipGetLastError();
 }
 
-template <class S, class C>
+// FP16 storage only: one-wave strips keep small lattices busy, large lattices take strips of whole
+// cache lines (192 columns) with 32 halo columns a side
 hipError_t launch_cp(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
-    // as for the pseudopotential step: one-wave strips keep small lattices busy, large lattices take
-    // strips of whole cache lines (224 FP32 / FP64 columns, 192 FP16) with 16 halo columns a side
-    if (c->g.N <= (int64_t(1) << 21)) return launch_cp_w<S, C, 64, 52>(c, fcur, rcur, fnext, rnext, pull);
-    if (sizeof(S) == 2) return launch_cp_w<S, C, 256, 192>(c, fcur, rcur, fnext, rnext, pull);
-    return launch_cp_w<S, C, 256, 224>(c, fcur, rcur, fnext, rnext, pull);
+    if (c->g.N <= (int64_t(1) << 21)) return launch_cp_w<__half, float, 64, 52>(c, fcur, rcur, fnext, rnext, pull);
+    return launch_cp_w<__half, float, 256, 192>(c, fcur, rcur, fnext, rnext, pull);
 }
 
 }  // namespace
@@ -957,20 +954,21 @@ hipError_t cp_wall_mu(mcb_ctx* c) {
 }
 
 hipError_t step2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
-    if (c->p.model == MCB_MODEL_CHEMPOT) {
-        switch (c->p.precision) {
-            case MCB_F64: return launch_cp<double, double>(c, fcur, rcur, fnext, rnext, pull);
-            case MCB_F32S: return launch_cp<float, float>(c, fcur, rcur, fnext, rnext, pull);
-            default: return launch_cp<__half, float>(c, fcur, rcur, fnext, rnext, pull);
-        }
-    }
-    // The tile kernels re-read a ring around every tile, the march a few halo rows and columns: where
-    // the two lattices stay in the 256 MB memory-side cache the ring costs little and the tiles' shorter
-    // chains win (FP32 1800 x 1500, 194 MB: 45 us against 77; FP16 2000 x 1850, 148 MB: 50 against 77;
-    // FP64 1531 x 1021, 225 MB: 49 against 81); past it the march does (FP32 2000 x 1850, 266 MB: 94
-    // against 111; FP16 2560 x 2500, 256 MB: 116 against 127; FP64 1400 x 1300, 262 MB: 88 against 84,
-    // 1800 x 1500, 389 MB: the same 125).
-    if (2 * state_bytes(c->p.precision, 9, c->g.N) <= TILE_BYTES) return tile2d(c, fcur, rcur, fnext, rnext, pull);
+    // FP16 storage keeps the marches.  A population is rounded to 11 bits, so where another kernel's
+    // code fuses another multiply-add, a few roundings per step go the other way, each far above the
+    // differences that caused it; within some tens of steps the states differ by the format's own
+    // rounding error everywhere (measured 5e-4 of f_0, with the same error against FP64).  A run of this
+    // storage repeats bit for bit as long as its kernel is the same.
+    // FP64 and FP32: the tile kernels re-read a ring around every tile, the march a few halo rows and
+    // columns.  Where the two lattices stay in the 256 MB memory-side cache the ring costs little and
+    // the tiles' shorter chains win (FP32 1800 x 1500, 194 MB: 43 us against 77; FP64 1531 x 1021,
+    // 225 MB: 47 against 81); past it the march does (FP32 2000 x 1850, 266 MB: 94 against 111;
+    // FP64 1400 x 1300, 262 MB: 88 against 84, 1800 x 1500, 389 MB: the same 125).  The chemical-
+    // potential model takes the tiles at every size.
+    const bool cp = c->p.model == MCB_MODEL_CHEMPOT;
+    if (c->p.precision != MCB_F16S && (cp || 2 * state_bytes(c->p.precision, 9, c->g.N) <= TILE_BYTES))
+        return tile2d(c, fcur, rcur, fnext, rnext, pull);
+    if (cp) return launch_cp(c, fcur, rcur, fnext, rnext, pull);
     switch (c->p.precision) {
         case MCB_F64: return launch_step2d<double, double>(c, fcur, rcur, fnext, rnext, pull);
         case MCB_F32S: return launch_step2d<float, float>(c, fcur, rcur, fnext, rnext, pull);

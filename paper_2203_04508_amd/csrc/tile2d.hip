@@ -1,43 +1,86 @@
-// D2Q9 step of small and middle-sized lattices: one workgroup computes one tile of the new state
-// (the same per-node arithmetic as the row marches of step2d.hip, which large lattices take).
+// D2Q9 step in tiles, FP64 and FP32 storage: one workgroup computes one tile of the new state (the same
+// per-node arithmetic as the row marches of step2d.hip).  Small and middle-sized lattices of the
+// pseudopotential model, all of the chemical-potential model's.
 #include "step2d_node.h"
 
 namespace mcb {
 namespace {
 
-// Offset, in a population plane, of the node that population i of node (cx, cy) is pulled from, from
-// the three columns and three rows around it.
-template <class S>
-struct Around {
-    uint32_t x[3], y[3];  // byte offsets of columns x + 1, x, x - 1 and of rows y + 1, y, y - 1: index e + 1
-};
-
-template <class S>
-__device__ __forceinline__ Around<S> around(int cx, int cy, int nx, int ny) {
-    constexpr uint32_t s = sizeof(S);
-    const uint32_t row = uint32_t(nx) * s;
-    return {{uint32_t(cx == nx - 1 ? 0 : cx + 1) * s, uint32_t(cx) * s, uint32_t(cx == 0 ? nx - 1 : cx - 1) * s},
-            {uint32_t(cy == ny - 1 ? 0 : cy + 1) * row, uint32_t(cy) * row, uint32_t(cy == 0 ? ny - 1 : cy - 1) * row}};
+// a buffer of at most BUF_MAX bytes (the boxes of this file are far below it)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t res32(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, int(bytes), 0x00020000);
 }
 
-// Issue the loads of the nine populations arriving at a node (eq. 5; PULL = false: its own).
-template <class S, class C, bool PULL>
-__device__ __forceinline__ void pull_at(__amdgpu_buffer_rsrc_t fa, uint32_t ns, const Around<S>& A, C (&f)[9]) {
+// Issue the loads of the nine populations arriving at node (cx, cy) (eq. 5, from x - e_i; PULL = false:
+// its own).  INNER: the node and its neighbours lie inside the box, so one lane offset serves all nine
+// and the rest of each address is uniform; otherwise the neighbours are wrapped one by one.
+template <class S, class C, bool PULL, bool INNER>
+__device__ __forceinline__ void pull_at(__amdgpu_buffer_rsrc_t fa, int cx, int cy, int nx, int ny, C (&f)[9]) {
+    constexpr uint32_t s = sizeof(S);
+    const uint32_t row = uint32_t(nx) * s, ns = row * uint32_t(ny);
+    const uint32_t o = uint32_t(cy) * row + uint32_t(cx) * s;
+    uint32_t xo[3], yo[3];  // columns x + 1, x, x - 1 and rows y + 1, y, y - 1: index e + 1
+    if (PULL && !INNER) {
+        xo[0] = uint32_t(cx == nx - 1 ? 0 : cx + 1) * s;
+        xo[1] = uint32_t(cx) * s;
+        xo[2] = uint32_t(cx == 0 ? nx - 1 : cx - 1) * s;
+        yo[0] = uint32_t(cy == ny - 1 ? 0 : cy + 1) * row;
+        yo[1] = uint32_t(cy) * row;
+        yo[2] = uint32_t(cy == 0 ? ny - 1 : cy - 1) * row;
+    }
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        const uint32_t o = PULL ? A.x[kEx[i] + 1] + A.y[kEy[i] + 1] : A.x[1] + A.y[1];
-        if (kMixed<S> && i == 0)
-            f[0] = Buf<float>::ld(fa, o * 2u);  // FP16 storage: the rest population in FP32
+        if (PULL && !INNER)
+            f[i] = Buf<S>::ld(fa, xo[kEx[i] + 1] + yo[kEy[i] + 1], uint32_t(i) * ns);
         else
-            f[i] = Buf<S>::ld(fa, o, uint32_t(i + (kMixed<S> ? 1 : 0)) * ns);
+            f[i] = Buf<S>::ld(fa, o, uint32_t(i) * ns - (PULL ? uint32_t(kEy[i]) * row + uint32_t(kEx[i]) * s : 0u));
     }
 }
 
-// periodic image of a coordinate v >= -2 (m >= 3; one subtraction unless the box is smaller than a tile)
+// The new state of a node (offset xst in a population plane, or OOB: not stored): its populations, zeros
+// on solid nodes (the pull replaces what it takes from them), and a boundary node's record.
+template <class S, class C>
+__device__ __forceinline__ void store_node(__amdgpu_buffer_rsrc_t fb, __amdgpu_buffer_rsrc_t rout, uint32_t ns, uint32_t xst,
+                                           bool coll, int tg, const C (&out)[9], C rho, C dux, C duy, C sx2, C sy2, C duu15,
+                                           C ds) {
+    constexpr uint32_t sc = sizeof(C);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Buf<S>::st(fb, sat_add(xst, uint32_t(i) * ns), coll ? out[i] : C(0));
+    if (__any(coll && tg > 0)) {
+        C rv[REC2];
+        rv[0] = rho;
+        rv[1] = dux;
+        rv[2] = duy;
+        rv[3] = sx2;
+        rv[4] = sy2;
+        rv[5] = duu15;
+#pragma unroll
+        for (int i = 1; i < 9; ++i) rv[RF2 + i - 1] = out[i];  // rounded to the storage format
+        C sl = C(0);  // the populations on the node's links (tag bits 0 .. 7)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sl += ((tg >> j) & 1) ? out[j + 1] : C(0);
+        rv[RF2 + 8] = sl;
+        rv[RF2 + 9] = ds;
+        st_vec(rout, (coll && tg > 0) ? uint32_t(tg >> 8) * (REC2 * sc) : OOB, rv);
+    }
+}
+
+// periodic image of a coordinate (at most one addition or subtraction unless the box is smaller than
+// a tile and its ring)
 __device__ __forceinline__ int image(int v, int m) {
-    v = v < 0 ? v + m : v;
+    while (v < 0) v += m;
     while (v >= m) v -= m;
     return v;
+}
+
+// Entry j of the ring of H nodes around a TX x TY tile, in the coordinates of the (TX + 2 H) x (TY + 2 H)
+// region: H rows below, H above, then H columns on either side of each tile row.
+template <int TX, int TY, int H>
+__device__ __forceinline__ void ring_at(int j, int& rx, int& ry) {
+    constexpr int RX = TX + 2 * H;
+    const int q = j - 2 * H * RX;
+    ry = q < 0 ? (j < H * RX ? j / RX : TY + j / RX) : q / (2 * H) + H;
+    rx = q < 0 ? j % RX : (q % (2 * H) < H ? q % (2 * H) : TX + q % (2 * H));
 }
 
 // ---------------------------------------------------------------- pseudopotential model
@@ -65,7 +108,7 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
     constexpr int RX = TX + 4, RY = TY + 4, PX = TX + 2, PY = TY + 2;
     constexpr int NRING = RX * RY - TX * TY, NRL = (NRING + NT - 1) / NT;
     constexpr int NP = PX * PY, NPL = (NP + NT - 1) / NT;
-    constexpr uint32_t s = sizeof(S), sc = sizeof(C), P0 = kMixed<S> ? 1 : 0;
+    constexpr uint32_t s = sizeof(S), sc = sizeof(C);
     __shared__ C s_rho[RY * RX];
     __shared__ C s_psi[PY * PX];
     // XCD-aware order: consecutive tiles go to the same XCD (one L2)
@@ -76,13 +119,10 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
     const int x0 = (logical % a.nsx) * TX, y0 = (logical / a.nsx) * TY;
     const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = a.nx, ny = a.ny;
     const uint32_t n = uint32_t(nx) * uint32_t(ny), ns = n * s;
-    const __amdgpu_buffer_rsrc_t rfa = make_res(a.fa, uint64_t(9 + P0) * ns);
-    const __amdgpu_buffer_rsrc_t rfb = make_res(a.fb, uint64_t(9 + P0) * ns);
-    const __amdgpu_buffer_rsrc_t rtag = make_res(a.tag, uint64_t(n) * 4);
-    const __amdgpu_buffer_rsrc_t rin = make_res(a.rin, uint64_t(a.n_bnodes) * REC2 * sc);
-    const __amdgpu_buffer_rsrc_t rout = make_res(a.rout, uint64_t(a.n_bnodes) * REC2 * sc);
-    const __amdgpu_buffer_rsrc_t rla = make_res(a.la, uint64_t(a.n_bnodes) * Q2_LINKS * sc);
-    const __amdgpu_buffer_rsrc_t rfac = make_res(a.fac, uint64_t(a.n_wall) * sc);
+    const __amdgpu_buffer_rsrc_t rfa = res32(a.fa, 9u * ns), rfb = res32(a.fb, 9u * ns);
+    const __amdgpu_buffer_rsrc_t rtag = res32(a.tag, n * 4u), rfac = res32(a.fac, a.n_wall * sc);
+    const __amdgpu_buffer_rsrc_t rin = res32(a.rin, a.n_bnodes * (REC2 * sc)), rout = res32(a.rout, a.n_bnodes * (REC2 * sc));
+    const __amdgpu_buffer_rsrc_t rla = res32(a.la, a.n_bnodes * (Q2_LINKS * sc));
     // the density of a boundary node where eq. 18 applies: f_in enters its sum once and is subtracted
     // once from f_0, which leaves the node's own populations on its links; its record holds their sum
     const bool link_sum = PULL && a.k18 != C(0);
@@ -91,29 +131,30 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
     // ---- 1: tags first, then the populations (the loads that depend on a tag follow both)
     int tg[RPL], tgr[NRL], pr[NRL];  // tags of the own and ring nodes, region entry of the ring nodes
     C f[RPL][9], fr[NRL][9];
-    Around<S> own[RPL], rng[NRL];
+    // INNER: the region and the nodes around it lie inside the box (all but the tiles along its edges)
+    auto load = [&](auto in) {
+        constexpr bool INNER = decltype(in)::value;
+        int cx[RPL + NRL], cy[RPL + NRL];
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int cx = image(x0 + lx, nx), cy = image(y0 + ly + r * LY, ny);
-        own[r] = around<S>(cx, cy, nx, ny);
-        tg[r] = ld_i32(rtag, (uint32_t(cy) * uint32_t(nx) + uint32_t(cx)) * 4u);
-    }
+        for (int k = 0; k < RPL + NRL; ++k) {
+            int rx = lx + 2, ry = ly + k * LY + 2;
+            if (k >= RPL) {
+                // lanes past the ring's last entry repeat it
+                ring_at<TX, TY, 2>(min(t + (k - RPL) * NT, NRING - 1), rx, ry);
+                pr[k - RPL] = ry * RX + rx;
+            }
+            cx[k] = INNER ? x0 - 2 + rx : image(x0 - 2 + rx, nx);
+            cy[k] = INNER ? y0 - 2 + ry : image(y0 - 2 + ry, ny);
+            (k < RPL ? tg[k < RPL ? k : 0] : tgr[k < RPL ? 0 : k - RPL]) = ld_i32(rtag, (uint32_t(cy[k]) * uint32_t(nx) + uint32_t(cx[k])) * 4u);
+        }
 #pragma unroll
-    for (int h = 0; h < NRL; ++h) {
-        // ring entries: two rows below, two above, then two columns on either side of each tile row;
-        // lanes past the last entry repeat it
-        const int j = min(t + h * NT, NRING - 1), q = j - 4 * RX;
-        const int ry = j < 4 * RX ? (j < 2 * RX ? j / RX : TY + j / RX) : q / 4 + 2;
-        const int rx = j < 4 * RX ? j % RX : ((q & 3) < 2 ? (q & 3) : TX + (q & 3));
-        pr[h] = ry * RX + rx;
-        const int cx = image(x0 - 2 + rx, nx), cy = image(y0 - 2 + ry, ny);
-        rng[h] = around<S>(cx, cy, nx, ny);
-        tgr[h] = ld_i32(rtag, (uint32_t(cy) * uint32_t(nx) + uint32_t(cx)) * 4u);
-    }
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) pull_at<S, C, PULL>(rfa, ns, own[r], f[r]);
-#pragma unroll
-    for (int h = 0; h < NRL; ++h) pull_at<S, C, PULL>(rfa, ns, rng[h], fr[h]);
+        for (int k = 0; k < RPL + NRL; ++k)
+            pull_at<S, C, PULL, INNER>(rfa, cx[k], cy[k], nx, ny, k < RPL ? f[k < RPL ? k : 0] : fr[k < RPL ? 0 : k - RPL]);
+    };
+    if (x0 >= 3 && y0 >= 3 && x0 + TX + 3 <= nx && y0 + TY + 3 <= ny)
+        load(std::true_type{});
+    else
+        load(std::false_type{});
     C ds[RPL], er[RPL];
     auto sum9 = [](const C (&v)[9]) {
         C sr = C(0);
@@ -205,32 +246,9 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
         C out[9];
         C rho, dux, duy, sx2, sy2, duu15;
         collide9<S, C, MRT>(a, coll, f[r], rs_acc, Fx, Fy, out, rho, dux, duy, sx2, sy2, duu15);
-        // solid nodes store zeros (the pull replaces what it takes from them)
-        const uint32_t xst = out_node ? own[r].x[1] + own[r].y[1] : OOB;
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            if (kMixed<S> && i == 0)
-                Buf<float>::st(rfb, xst == OOB ? OOB : xst * 2u, coll ? out[0] : C(0));
-            else
-                Buf<S>::st(rfb, sat_add(xst, uint32_t(i + P0) * ns), coll ? out[i] : C(0));
-        }
-        if (__any(coll && tg[r] > 0)) {
-            C rv[REC2];
-            rv[0] = rho;
-            rv[1] = dux;
-            rv[2] = duy;
-            rv[3] = sx2;
-            rv[4] = sy2;
-            rv[5] = duu15;
-#pragma unroll
-            for (int i = 1; i < 9; ++i) rv[RF2 + i - 1] = out[i];  // rounded to the storage format
-            C sl = C(0);  // the populations on the node's links (tag bits 0 .. 7)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) sl += ((tg[r] >> j) & 1) ? out[j + 1] : C(0);
-            rv[RF2 + 8] = sl;
-            rv[RF2 + 9] = ds[r];
-            st_vec(rout, (coll && tg[r] > 0) ? uint32_t(tg[r] >> 8) * (REC2 * sc) : OOB, rv);
-        }
+        const uint32_t x = uint32_t(y0 + ly + r * LY) * uint32_t(nx) + uint32_t(x0 + lx);
+        store_node<S, C>(rfb, rout, ns, out_node ? x * s : OOB, coll, tg[r], out, rho, dux, duy, sx2, sy2,
+                         duu15, ds[r]);
     }
     if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
 }
@@ -262,14 +280,248 @@ hipError_t tile_t(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, v
     return launch_tile<S, C, 32, 256, 1, WPE>(c, fcur, rcur, fnext, rnext, pull);
 }
 
+// ---------------------------------------------------------------- chemical-potential model
+// The same with a wider reach.  The collision of a node needs mu and rho two nodes away on each axis
+// (eq. 9), mu of a fluid node rho two nodes away (eq. 12), the second solid layer's density the first
+// layer's around it, and the first layer's the fluid densities around it (eq. 15): densities up to
+// six nodes away.  Five phases:
+//   1  own nodes and the ring six nodes wide: pulled density and solid layer, to LDS.  Where eq. 18
+//      applies, a boundary node's density is its pulled populations plus the link sum of its record;
+//      without it (IBC) eqs. 16-17 run on the ring too;
+//   2  the first solid layer's density, 3 the second's (skipped by tiles without solid nodes);
+//   4  mu of the tile and two nodes around it (eq. 12; solid nodes take their assigned values);
+//   5  force from both fields, eqs. 16-18 and the collision of the own nodes.
+// Measured against a march (one row per iteration, five barriers a row) that this replaces: 500 x 300
+// FP64 102 -> 20 us a step on a flat wall, 1024^2 FP32 on balls 144 -> 31, FP64 184 -> 58, 4096^2 FP32
+// 483 -> 480, FP64 1048 -> 959.  Vector instructions bound it on large boxes.
+// Taking the tiles in groups of 2, 4 or 8 rows, column by column, so that fewer rings cross an
+// XCD's L2, measured slower at 4096^2 (FP32 482, 522, 506 us against 482).
+template <class S, class C, int TX, int NT, int RPL, int WPE, bool PULL, bool MRT>
+__global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
+    constexpr int HC = 6, LY = NT / TX, TY = LY * RPL;
+    constexpr int RX = TX + 2 * HC, RY = TY + 2 * HC, NR = RX * RY, NRH = (NR + NT - 1) / NT;
+    constexpr int MX = TX + 4, MY = TY + 4, NM = MX * MY, NML = (NM + NT - 1) / NT;
+    constexpr int NRING = NR - TX * TY, NRL = (NRING + NT - 1) / NT;
+    constexpr uint32_t s = sizeof(S), sc = sizeof(C);
+    const Args2<S, C>& a = p.a;
+    __shared__ C s_rho[NR];
+    __shared__ C s_mu[NM];
+    __shared__ int8_t s_lay[NR];
+    const int bid = blockIdx.x;
+    const int per = a.nblocks >> 3, rem = a.nblocks & 7;
+    const int xcd = bid & 7, k8 = bid >> 3;
+    const int logical = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + k8;
+    const int x0 = (logical % a.nsx) * TX, y0 = (logical / a.nsx) * TY;
+    const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = a.nx, ny = a.ny;
+    const uint32_t n = uint32_t(nx) * uint32_t(ny), ns = n * s;
+    const __amdgpu_buffer_rsrc_t rfa = res32(a.fa, 9u * ns), rfb = res32(a.fb, 9u * ns);
+    const __amdgpu_buffer_rsrc_t rtag = res32(a.tag, n * 4u), rlay = res32(p.layer, n), rmu = res32(p.mu, n * sc);
+    const __amdgpu_buffer_rsrc_t rin = res32(a.rin, a.n_bnodes * (REC2 * sc)), rout = res32(a.rout, a.n_bnodes * (REC2 * sc));
+    const __amdgpu_buffer_rsrc_t rla = res32(a.la, a.n_bnodes * (Q2_LINKS * sc));
+    const bool link_sum = PULL && a.k18 != C(0);
+    bool bad = false, solid = false;
+
+    // ---- 1
+    int tg[RPL];
+    C f[RPL][9], ds[RPL], er[RPL];
+    // region entry of a node: layer lay, density from its pulled populations v and addend
+    auto put = [&](int at, int g, int lay, const C (&v)[9], C addend) {
+        MassAcc<S, C> rs = MassAcc<S, C>(0);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) rs += MassAcc<S, C>(v[i]);
+        rs += MassAcc<S, C>(addend);
+        s_rho[at] = g >= 0 ? C(rs) + a.rho_ref : C(0);
+        s_lay[at] = int8_t(lay);
+        solid = solid || lay == 1 || lay == 2;
+    };
+    auto links = [&](int g, C (&v)[9], C& d, C& e) {
+        C rec[RF2 + 9], head[RF2 + 8], ca[Q2_LINKS];
+        const uint32_t bi = uint32_t(g >> 8);
+        ld_vec(rin, g > 0 ? bi * (REC2 * sc) : OOB, rec);
+        ld_vec(rla, g > 0 ? bi * (Q2_LINKS * sc) : OOB, ca);
+#pragma unroll
+        for (int i = 0; i < RF2 + 8; ++i) head[i] = rec[i];
+        d = apply_links<S, C>(g > 0, head, ca, v, a.kF, a.k18, e);
+        return rec[RF2 + 8];
+    };
+    int lay[RPL];
+    C mus[NML];  // the solid nodes' assigned potentials of the mu region (fluid nodes' entries are not used)
+    auto load = [&](auto in) {
+        constexpr bool INNER = decltype(in)::value;
+        auto coord = [&](int rx, int ry, int& cx, int& cy) {
+            cx = INNER ? x0 - HC + rx : image(x0 - HC + rx, nx);
+            cy = INNER ? y0 - HC + ry : image(y0 - HC + ry, ny);
+            return uint32_t(cy) * uint32_t(nx) + uint32_t(cx);
+        };
+        int cx[RPL + NRL], cy[RPL + NRL], tgr[NRL], layr[NRL], pr[NRL];
+#pragma unroll
+        for (int k = 0; k < RPL + NRL; ++k) {
+            int rx = lx + HC, ry = ly + k * LY + HC;
+            if (k >= RPL) {
+                ring_at<TX, TY, HC>(min(t + (k - RPL) * NT, NRING - 1), rx, ry);
+                pr[k - RPL] = ry * RX + rx;
+            }
+            const uint32_t x = coord(rx, ry, cx[k], cy[k]);
+            (k < RPL ? tg[k < RPL ? k : 0] : tgr[k < RPL ? 0 : k - RPL]) = ld_i32(rtag, x * 4u);
+            (k < RPL ? lay[k < RPL ? k : 0] : layr[k < RPL ? 0 : k - RPL]) =
+                int8_t(__builtin_amdgcn_raw_buffer_load_b8(rlay, x, 0, 0));
+        }
+#pragma unroll
+        for (int h = 0; h < NML; ++h) {
+            const int j = min(t + h * NT, NM - 1);
+            int mx, my;
+            mus[h] = Buf<C>::ld(rmu, coord(j % MX + HC - 2, j / MX + HC - 2, mx, my) * sc);
+        }
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) pull_at<S, C, PULL, INNER>(rfa, cx[r], cy[r], nx, ny, f[r]);
+#pragma unroll
+        for (int h = 0; h < NRL; ++h) {
+            C v[9], ls = C(0);
+            pull_at<S, C, PULL, INNER>(rfa, cx[RPL + h], cy[RPL + h], nx, ny, v);
+            if (link_sum) {
+                ls = Buf<C>::ld(rin, tgr[h] > 0 ? uint32_t(tgr[h] >> 8) * (REC2 * sc) + (RF2 + 8) * sc : OOB);
+            } else if (PULL && __any(tgr[h] > 0)) {
+                C d;
+                links(tgr[h], v, d, ls);
+            }
+            put(pr[h], tgr[h], layr[h], v, ls);
+        }
+    };
+    if (x0 > HC && y0 > HC && x0 + TX + HC + 1 <= nx && y0 + TY + HC + 1 <= ny)
+        load(std::true_type{});
+    else
+        load(std::false_type{});
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+        const int at = (ly + r * LY + HC) * RX + lx + HC;
+        ds[r] = er[r] = C(0);
+        if (PULL && __any(tg[r] > 0)) {
+            C v[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) v[i] = f[r][i];
+            const C ls = links(tg[r], f[r], ds[r], er[r]);
+            if (link_sum)
+                put(at, tg[r], lay[r], v, tg[r] > 0 ? ls : C(0));
+            else
+                put(at, tg[r], lay[r], f[r], er[r]);
+        } else {
+            put(at, tg[r], lay[r], f[r], C(0));
+        }
+    }
+    // ---- 2, 3: the solid layers (eq. 15 over the layer above), where the tile's region holds any
+    if (__syncthreads_or(solid)) {
+#pragma unroll 1
+        for (int l = 1; l <= 2; ++l) {
+#pragma unroll
+            for (int h = 0; h < NRH; ++h) {
+                const int e = t + h * NT, ex = e % RX, ey = e / RX;
+                if (e < NR && ex >= l && ex < RX - l && ey >= l && ey < RY - l && s_lay[e] == l) {
+                    // every neighbour's layer and density first, then the selection
+                    int nl[9];
+                    C nr[9];
+#pragma unroll
+                    for (int i = 1; i < 9; ++i) {
+                        nl[i] = s_lay[e + kEy[i] * RX + kEx[i]];
+                        nr[i] = s_rho[e + kEy[i] * RX + kEx[i]];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    C num = C(0), den = C(0);
+#pragma unroll
+                    for (int i = 1; i < 9; ++i) {
+                        num += nl[i] == l - 1 ? w9<C>(i) * nr[i] : C(0);
+                        den += nl[i] == l - 1 ? w9<C>(i) : C(0);
+                    }
+                    s_rho[e] = num / den;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    // ---- 4: chemical potential (eq. 12 with the Peng-Robinson mu of eq. 11)
+    const C s2 = C(1.4142135623730951);
+#pragma unroll
+    for (int h = 0; h < NML; ++h) {
+        const int j = t + h * NT;
+        if (j < NM) {
+            const int e = (j / MX + HC - 2) * RX + j % MX + HC - 2;
+            C m = mus[h];
+            if (s_lay[e] == 0) {
+                const C rc = s_rho[e];
+                const C br = p.b * rc;
+                if (!(rc > C(0)) || !(br < C(1))) bad = true;
+                const C rf = rc > C(0) && br < C(1) ? rc : C(1);  // a harmless stand-in past the domain
+                const C brf = p.b * rf;
+                const C iq = rcp(C(1) - brf);
+                const C m0 = p.RT * log(rf * iq) - p.c_log * log((s2 - C(1) + brf) * rcp(s2 + C(1) - brf)) +
+                             p.RT * iq - p.aal * rf * rcp(C(1) + C(2) * brf - brf * brf);
+                C lap = C(0);
+                lap += cd2(s_rho[e - 2], s_rho[e - 1], rc, s_rho[e + 1], s_rho[e + 2]);
+                lap += cd2(s_rho[e - 2 * RX], s_rho[e - RX], rc, s_rho[e + RX], s_rho[e + 2 * RX]);
+                m = p.k2 * m0 - p.kappa * lap;
+            }
+            s_mu[j] = m;
+        }
+    }
+    __syncthreads();
+    // ---- 5: force, collision, store
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+        const bool out_node = x0 + lx < nx && y0 + ly + r * LY < ny;
+        const bool coll = out_node && tg[r] >= 0;
+        MassAcc<S, C> rs = MassAcc<S, C>(er[r]);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) rs += MassAcc<S, C>(f[r][i]);
+        const C* R = s_rho + (ly + r * LY + HC) * RX + lx + HC;
+        const C* U = s_mu + (ly + r * LY + 2) * MX + lx + 2;
+        const C rr = R[0];
+        const C Fx = -rr * cd1(U[-2], U[-1], U[1], U[2]) + cd1(R[-2], R[-1], R[1], R[2]) / C(3);
+        const C Fy = -rr * cd1(U[-2 * MX], U[-MX], U[MX], U[2 * MX]) + cd1(R[-2 * RX], R[-RX], R[RX], R[2 * RX]) / C(3);
+        C out[9];
+        C rho, dux, duy, sx2, sy2, duu15;
+        collide9<S, C, MRT>(a, coll, f[r], rs, coll ? Fx : C(0), coll ? Fy : C(0), out, rho, dux, duy, sx2, sy2, duu15);
+        const uint32_t x = uint32_t(y0 + ly + r * LY) * uint32_t(nx) + uint32_t(x0 + lx);
+        store_node<S, C>(rfb, rout, ns, out_node ? x * s : OOB, coll, tg[r], out, rho, dux, duy, sx2, sy2,
+                         duu15, ds[r]);
+    }
+    if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
+}
+
+template <class S, class C, int TX, int NT, int RPL, int WPE>
+hipError_t launch_cptile(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
+    constexpr int TY = NT / TX * RPL;
+    ArgsCP<S, C> p = cp_args<S, C>(c, fcur, rcur, fnext, rnext);
+    p.a.nsx = (p.a.nx + TX - 1) / TX;
+    p.a.nblocks = p.a.nsx * ((p.a.ny + TY - 1) / TY);
+    const bool mrt = c->p.collision == MCB_COLL_MRT;
+    const auto k = pull ? (mrt ? k_cptile<S, C, TX, NT, RPL, WPE, true, true> : k_cptile<S, C, TX, NT, RPL, WPE, true, false>)
+                        : (mrt ? k_cptile<S, C, TX, NT, RPL, WPE, false, true> : k_cptile<S, C, TX, NT, RPL, WPE, false, false>);
+    hipLaunchKernelGGL(k, dim3(unsigned(p.a.nblocks)), dim3(NT), 0, c->stream, p);
+    return hipGetLastError();
+}
+
+// 32 x 32 tiles of two nodes a lane pull 0.9 ring nodes per node, 32 x 16 tiles of one node a lane 1.4, but
+// run a shorter chain; the larger ones are taken once the box holds two of them per compute unit
+// (1024^2 FP64 58 us against 62, 2048 x 1024 FP32 52 against 56, 4096^2 FP32 480 against 534; 512^2 FP64,
+// one a unit, 24 against 21, 724^2 42 against 38).  FP32 arithmetic fits 80 VGPRs, six waves per
+// SIMD; FP64 is held to 128 (a 36-byte spill): unbounded, at three waves, 1024^2 took 78 us against 60.
+template <class S, class C>
+hipError_t cptile_t(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
+    constexpr int WPE = sizeof(C) == 8 ? 4 : 6;
+    const int64_t tiles = int64_t((c->p.nx + 31) / 32) * ((c->p.ny + 31) / 32);
+    if (tiles >= 2 * c->n_cu) return launch_cptile<S, C, 32, 512, 2, WPE>(c, fcur, rcur, fnext, rnext, pull);
+    return launch_cptile<S, C, 32, 512, 1, WPE>(c, fcur, rcur, fnext, rnext, pull);
+}
+
 }  // namespace
 
+// FP16 storage stays with the row marches (see step2d)
 hipError_t tile2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
-    switch (c->p.precision) {
-        case MCB_F64: return tile_t<double, double>(c, fcur, rcur, fnext, rnext, pull);
-        case MCB_F32S: return tile_t<float, float>(c, fcur, rcur, fnext, rnext, pull);
-        default: return tile_t<__half, float>(c, fcur, rcur, fnext, rnext, pull);
-    }
+    const bool f64 = c->p.precision == MCB_F64;
+    if (c->p.model == MCB_MODEL_CHEMPOT)
+        return f64 ? cptile_t<double, double>(c, fcur, rcur, fnext, rnext, pull)
+                   : cptile_t<float, float>(c, fcur, rcur, fnext, rnext, pull);
+    return f64 ? tile_t<double, double>(c, fcur, rcur, fnext, rnext, pull)
+               : tile_t<float, float>(c, fcur, rcur, fnext, rnext, pull);
 }
 
 }  // namespace mcb
