@@ -104,7 +104,6 @@ AdjPlan adj_plan(const mcb_ctx* c, int64_t nsteps, int64_t k) {
     a.rbar = take(8 * N);
     a.qbar = take(8 * N);
     a.Fbar = take(8 * 3 * N);
-    a.Fv = take(8 * 3 * N);
     a.dphi = take(8 * (c->n_wall > 0 ? c->n_wall : 1));
     a.part = take(8 * 2 * MON_BLOCKS);
     a.sums = take(8 * 2);
@@ -606,7 +605,6 @@ static AdjWork adj_work(mcb_ctx* c) {
     w.rbar = d(a.rbar);
     w.qbar = d(a.qbar);
     w.Fbar = d(a.Fbar);
-    w.Fv = d(a.Fv);
     w.dphi = d(a.dphi);
     w.part = d(a.part);
     w.sums = d(a.sums);
