@@ -268,7 +268,7 @@ def main():
         "roofline": {
             "bound": "hbm",
             "kernel": ("k_cptile (one step)" if args.model == "chempot"
-                       else "k_step2d" if wl.dim == 2 else "k_rho3d + k_step3d (one step)"),
+                       else "k_step2d" if wl.dim == 2 else "k_rho3f + k_psi3w + k_collide3f (one step)"),
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

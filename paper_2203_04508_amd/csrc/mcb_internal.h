@@ -177,6 +177,8 @@ hipError_t step_fused(mcb_ctx* c, const void* fcur, const void* rcur, void* fnex
 // tile2d.hip: the D2Q9 step where both lattices together hold at most TILE_BYTES
 constexpr int64_t TILE_BYTES = 240000000;
 hipError_t tile2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull);
+// flat3d.hip: the D3Q19 step of FP64 and FP32 storage
+hipError_t flat3d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull);
 hipError_t init_feq(mcb_ctx* c, const double* rho, const double* u, void* fout);
 
 // adjoint.hip: one transposed step (pull = 0: the first collision from f^eq(rho0, 0)), and the

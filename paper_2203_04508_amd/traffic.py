@@ -32,7 +32,7 @@ def kernel_digest(dim: int) -> str:
     """Hash of the sources the step kernel of a dimension is built from: counters taken on another
     version of the kernel do not describe this one."""
     h = hashlib.sha256()
-    for f in (*(("step2d.hip", "tile2d.hip", "step2d_node.h") if dim == 2 else ("step3d.hip",)), "kernels_common.h", "mcb_internal.h"):
+    for f in (*(("step2d.hip", "tile2d.hip", "step2d_node.h") if dim == 2 else ("step3d.hip", "flat3d.hip", "step3d_node.h")), "kernels_common.h", "mcb_internal.h"):
         h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -99,17 +99,19 @@ def _largest(rows, match):
 def _pull_kernel(name):
     """The per-step kernels of the pulling step (not the collision that starts a run), by name:
     k_step2d<S, C, W, OUT, PULL>, k_step3d<S, C, PULL, PF>, k_rho3d<S, C, PULL>,
+    k_rho3f<S, C, PULL, IBC>, k_collide3f<S, C, PULL> (and k_psi3w, which every step runs),
     k_tile2d<S, C, TX, NT, RPL, WPE, PULL>, k_cptile<S, C, TX, NT, RPL, WPE, PULL>, and
     k_cp_march<S, C, W, OUT, PULL> of older databases."""
-    for k, idx in (("k_step2d<", 4), ("k_step3d<", 2), ("k_rho3d<", 2), ("k_tile2d<", 6), ("k_cptile<", 6), ("k_cp_march<", 4)):
+    for k, idx in (("k_step2d<", 4), ("k_step3d<", 2), ("k_rho3d<", 2), ("k_tile2d<", 6), ("k_cptile<", 6), ("k_cp_march<", 4),
+                   ("k_rho3f<", 2), ("k_collide3f<", 2)):
         if k in name:
             args = name.split(k, 1)[1].split(">", 1)[0].split(",")
             return len(args) > idx and args[idx].strip() == "true"
-    return False
+    return "k_psi3w<" in name
 
 
 def _short(name):
-    for k in ("k_step2d", "k_step3d", "k_rho3d", "k_tile2d", "k_cptile", "k_cp_march"):
+    for k in ("k_step2d", "k_step3d", "k_rho3d", "k_tile2d", "k_cptile", "k_cp_march", "k_rho3f", "k_psi3w", "k_collide3f"):
         if k in name:
             return k
     return name
@@ -145,7 +147,7 @@ def summarize(args):
         kk["bytes_per_launch"] = kk.get("read_bytes_per_launch", 0.0) + kk.get("write_bytes_per_launch", 0.0)
         step += kk["bytes_per_launch"]
     # the step kernel proper (the collision pass in three dimensions) is the one bench.py reports
-    main = next((out["kernels"][k] for k in ("k_step2d", "k_step3d", "k_tile2d", "k_cptile", "k_cp_march")
+    main = next((out["kernels"][k] for k in ("k_step2d", "k_step3d", "k_collide3f", "k_tile2d", "k_cptile", "k_cp_march")
                  if k in out["kernels"]), None)
     out["bytes_per_launch"] = main["bytes_per_launch"] if main else None
     out["bytes_per_step"] = step
