@@ -368,12 +368,13 @@ hipError_t launch_w(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext,
 
 template <class S, class C>
 hipError_t launch_step2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
-    // strips a whole number of cache lines wide (224 FP32 / FP64 columns, 192 FP16 columns), so that
-    // no line is shared between strips or written in parts; small boxes (FP16 storage alone comes
-    // here with them) take one-wave strips, which keep more workgroups busy
+    // strips of 224 columns: a whole number of cache lines with FP64 and FP32 storage, so that no line is
+    // shared between strips or written in parts.  With FP16 storage 3.5 lines: the shared half costs less
+    // than the 32 lanes that strips of 192 columns leave idle (4096^2 267 -> 260 us a step, 3000 x 3100
+    // 160 -> 157, 2100 x 2048 the same 86).  Small boxes (FP16 storage alone comes here with them) take
+    // one-wave strips, which keep more workgroups busy.
     if constexpr (sizeof(S) == 2)
         if (c->g.N <= (int64_t(1) << 21)) return launch_w<S, C, 64, 60>(c, fcur, rcur, fnext, rnext, pull);
-    if (sizeof(S) == 2) return launch_w<S, C, 256, 192>(c, fcur, rcur, fnext, rnext, pull);
     return launch_w<S, C, 256, 224>(c, fcur, rcur, fnext, rnext, pull);
 }
 
