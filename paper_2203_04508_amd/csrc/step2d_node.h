@@ -171,6 +171,7 @@ struct ArgsCP {
     C* mu;                  // chemical potential of the step: fluid nodes and solid layers 1-2
     const int8_t* layer;    // 0 fluid, 1 wall node, 2 second solid layer, 3 deeper
     const double* mus;      // assigned chemical potential per wall node
+    int nt;                 // populations stored non-temporally
     C k2, kappa;            // eq. 12: k^2 and kappa
     C RT, b, c_log, aal;    // eq. 11: R T, b, a alpha / (2 sqrt 2 b), a alpha
 };
@@ -233,6 +234,7 @@ ArgsCP<S, C> cp_args(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext
     p.a.fac = nullptr;  // no eq. 15 factors and no pseudopotential in this model
     p.a.G = C(0);
     p.a.eos = Eos<C>{};
+    p.nt = 0;
     p.rho = reinterpret_cast<C*>(c->lat + c->L.cp_rho);
     p.mu = reinterpret_cast<C*>(c->lat + c->L.cp_mu);
     p.layer = reinterpret_cast<const int8_t*>(c->lat + c->L.cp_layer);

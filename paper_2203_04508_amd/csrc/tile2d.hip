@@ -38,14 +38,20 @@ __device__ __forceinline__ void pull_at(__amdgpu_buffer_rsrc_t fa, int cx, int c
 }
 
 // The new state of a node (offset xst in a population plane, or OOB: not stored): its populations, zeros
-// on solid nodes (the pull replaces what it takes from them), and a boundary node's record.
+// on solid nodes (the pull replaces what it takes from them), and a boundary node's record.  nt (uniform):
+// the populations with non-temporal stores.
 template <class S, class C>
-__device__ __forceinline__ void store_node(__amdgpu_buffer_rsrc_t fb, __amdgpu_buffer_rsrc_t rout, uint32_t ns, uint32_t xst,
-                                           bool coll, int tg, const C (&out)[9], C rho, C dux, C duy, C sx2, C sy2, C duu15,
+__device__ __forceinline__ void store_node(bool nt, __amdgpu_buffer_rsrc_t fb, __amdgpu_buffer_rsrc_t rout, uint32_t ns,
+                                           uint32_t xst, bool coll, int tg, const C (&out)[9], C rho, C dux, C duy, C sx2, C sy2, C duu15,
                                            C ds) {
     constexpr uint32_t sc = sizeof(C);
+    if (nt) {
 #pragma unroll
-    for (int i = 0; i < 9; ++i) Buf<S>::st(fb, sat_add(xst, uint32_t(i) * ns), coll ? out[i] : C(0));
+        for (int i = 0; i < 9; ++i) Buf<S>::st_nt(fb, sat_add(xst, uint32_t(i) * ns), coll ? out[i] : C(0));
+    } else {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) Buf<S>::st(fb, sat_add(xst, uint32_t(i) * ns), coll ? out[i] : C(0));
+    }
     if (__any(coll && tg > 0)) {
         C rv[REC2];
         rv[0] = rho;
@@ -247,7 +253,7 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
         C rho, dux, duy, sx2, sy2, duu15;
         collide9<S, C, MRT>(a, coll, f[r], rs_acc, Fx, Fy, out, rho, dux, duy, sx2, sy2, duu15);
         const uint32_t x = uint32_t(y0 + ly + r * LY) * uint32_t(nx) + uint32_t(x0 + lx);
-        store_node<S, C>(rfb, rout, ns, out_node ? x * s : OOB, coll, tg[r], out, rho, dux, duy, sx2, sy2,
+        store_node<S, C>(false, rfb, rout, ns, out_node ? x * s : OOB, coll, tg[r], out, rho, dux, duy, sx2, sy2,
                          duu15, ds[r]);
     }
     if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
@@ -292,14 +298,12 @@ hipError_t tile_t(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, v
 //   4  mu of the tile and two nodes around it (eq. 12; solid nodes take their assigned values);
 //   5  force from both fields, eqs. 16-18 and the collision of the own nodes.
 // Measured against a march (one row per iteration, five barriers a row) that this replaces: 500 x 300
-// FP64 102 -> 20 us a step on a flat wall, 1024^2 FP32 on balls 144 -> 31, FP64 184 -> 58, 4096^2 FP32
-// 483 -> 480, FP64 1048 -> 959.  Vector instructions bound it on large boxes.
-// Taking the tiles in groups of 2, 4 or 8 rows, column by column, so that fewer rings cross an
-// XCD's L2, measured slower at 4096^2 (FP32 482, 522, 506 us against 482).
+// FP64 102 -> 14 us a step on a flat wall, 1024^2 FP32 on balls 144 -> 30, FP64 184 -> 55, 4096^2 FP32
+// 483 -> 435, FP64 1048 -> 847.  Vector instructions bound it on large boxes.
 template <class S, class C, int TX, int NT, int RPL, int WPE, bool PULL, bool MRT>
 __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
     constexpr int HC = 6, LY = NT / TX, TY = LY * RPL;
-    constexpr int RX = TX + 2 * HC, RY = TY + 2 * HC, NR = RX * RY, NRH = (NR + NT - 1) / NT;
+    constexpr int RX = TX + 2 * HC, RY = TY + 2 * HC, NR = RX * RY;
     constexpr int MX = TX + 4, MY = TY + 4, NM = MX * MY, NML = (NM + NT - 1) / NT;
     constexpr int NRING = NR - TX * TY, NRL = (NRING + NT - 1) / NT;
     constexpr uint32_t s = sizeof(S), sc = sizeof(C);
@@ -311,7 +315,16 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
     const int per = a.nblocks >> 3, rem = a.nblocks & 7;
     const int xcd = bid & 7, k8 = bid >> 3;
     const int logical = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + k8;
-    const int x0 = (logical % a.nsx) * TX, y0 = (logical / a.nsx) * TY;
+    // consecutive tiles run along panels of a.H tile columns, so that the ring a tile shares with the one
+    // above it is still in the XCD's L2 when that one reads it
+    int pan = 0, rp = logical, pw = a.nsx;
+    if (a.nsx > a.H) {
+        const int per_pan = a.H * (a.nblocks / a.nsx);
+        pan = logical / per_pan;
+        rp = logical - pan * per_pan;
+        pw = min(a.H, a.nsx - pan * a.H);
+    }
+    const int rq = rp / pw, x0 = (pan * a.H + rp - rq * pw) * TX, y0 = rq * TY;
     const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = a.nx, ny = a.ny;
     const uint32_t n = uint32_t(nx) * uint32_t(ny), ns = n * s;
     const __amdgpu_buffer_rsrc_t rfa = res32(a.fa, 9u * ns), rfb = res32(a.fb, 9u * ns);
@@ -323,16 +336,24 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
 
     // ---- 1
     int tg[RPL];
-    C f[RPL][9], ds[RPL], er[RPL];
-    // region entry of a node: layer lay, density from its pulled populations v and addend
-    auto put = [&](int at, int g, int lay, const C (&v)[9], C addend) {
+    C f[RPL][9], ds[RPL];
+    // region entry of a node: layer l, density from the sum rs of its populations.  The lane keeps the
+    // entries it makes, to serve their solid layers itself: entry | layer << 16, layer 3 where the
+    // neighbours of a layer node do not all lie in the region (nothing reads those).
+    int ent[RPL + NRL];
+    auto put = [&](int k, int rx, int ry, int g, int l, MassAcc<S, C> rs) {
+        const int at = ry * RX + rx;
+        s_rho[at] = g >= 0 ? C(rs) + a.rho_ref : C(0);
+        s_lay[at] = int8_t(l);
+        const bool in = k < RPL || (rx >= l && rx < RX - l && ry >= l && ry < RY - l);
+        ent[k] = at | ((in ? l : 3) << 16);
+        solid = solid || l == 1 || l == 2;
+    };
+    auto sum9 = [](const C (&v)[9]) {
         MassAcc<S, C> rs = MassAcc<S, C>(0);
 #pragma unroll
         for (int i = 0; i < 9; ++i) rs += MassAcc<S, C>(v[i]);
-        rs += MassAcc<S, C>(addend);
-        s_rho[at] = g >= 0 ? C(rs) + a.rho_ref : C(0);
-        s_lay[at] = int8_t(lay);
-        solid = solid || lay == 1 || lay == 2;
+        return rs;
     };
     auto links = [&](int g, C (&v)[9], C& d, C& e) {
         C rec[RF2 + 9], head[RF2 + 8], ca[Q2_LINKS];
@@ -353,13 +374,14 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
             cy = INNER ? y0 - HC + ry : image(y0 - HC + ry, ny);
             return uint32_t(cy) * uint32_t(nx) + uint32_t(cx);
         };
-        int cx[RPL + NRL], cy[RPL + NRL], tgr[NRL], layr[NRL], pr[NRL];
+        int cx[RPL + NRL], cy[RPL + NRL], tgr[NRL], layr[NRL], px[NRL], py[NRL];
 #pragma unroll
         for (int k = 0; k < RPL + NRL; ++k) {
             int rx = lx + HC, ry = ly + k * LY + HC;
             if (k >= RPL) {
                 ring_at<TX, TY, HC>(min(t + (k - RPL) * NT, NRING - 1), rx, ry);
-                pr[k - RPL] = ry * RX + rx;
+                px[k - RPL] = rx;
+                py[k - RPL] = ry;
             }
             const uint32_t x = coord(rx, ry, cx[k], cy[k]);
             (k < RPL ? tg[k < RPL ? k : 0] : tgr[k < RPL ? 0 : k - RPL]) = ld_i32(rtag, x * 4u);
@@ -384,38 +406,35 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
                 C d;
                 links(tgr[h], v, d, ls);
             }
-            put(pr[h], tgr[h], layr[h], v, ls);
+            put(RPL + h, px[h], py[h], tgr[h], layr[h], sum9(v) + MassAcc<S, C>(ls));
         }
     };
     if (x0 > HC && y0 > HC && x0 + TX + HC + 1 <= nx && y0 + TY + HC + 1 <= ny)
         load(std::true_type{});
     else
         load(std::false_type{});
+    MassAcc<S, C> rs[RPL];  // what the collision hands back: the sum after eqs. 16-18
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
-        const int at = (ly + r * LY + HC) * RX + lx + HC;
-        ds[r] = er[r] = C(0);
+        ds[r] = C(0);
+        rs[r] = sum9(f[r]);
+        MassAcc<S, C> rd = rs[r];
         if (PULL && __any(tg[r] > 0)) {
-            C v[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) v[i] = f[r][i];
-            const C ls = links(tg[r], f[r], ds[r], er[r]);
-            if (link_sum)
-                put(at, tg[r], lay[r], v, tg[r] > 0 ? ls : C(0));
-            else
-                put(at, tg[r], lay[r], f[r], er[r]);
-        } else {
-            put(at, tg[r], lay[r], f[r], C(0));
+            C er;
+            const C ls = links(tg[r], f[r], ds[r], er);
+            rs[r] = sum9(f[r]) + MassAcc<S, C>(er);
+            rd = link_sum ? rd + MassAcc<S, C>(tg[r] > 0 ? ls : C(0)) : rs[r];
         }
+        put(r, lx + HC, ly + r * LY + HC, tg[r], lay[r], rd);
     }
     // ---- 2, 3: the solid layers (eq. 15 over the layer above), where the tile's region holds any
     if (__syncthreads_or(solid)) {
 #pragma unroll 1
         for (int l = 1; l <= 2; ++l) {
 #pragma unroll
-            for (int h = 0; h < NRH; ++h) {
-                const int e = t + h * NT, ex = e % RX, ey = e / RX;
-                if (e < NR && ex >= l && ex < RX - l && ey >= l && ey < RY - l && s_lay[e] == l) {
+            for (int h = 0; h < RPL + NRL; ++h) {
+                const int e = ent[h] & 0xFFFF;
+                if ((ent[h] >> 16) == l) {
                     // every neighbour's layer and density first, then the selection
                     int nl[9];
                     C nr[9];
@@ -468,9 +487,6 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
     for (int r = 0; r < RPL; ++r) {
         const bool out_node = x0 + lx < nx && y0 + ly + r * LY < ny;
         const bool coll = out_node && tg[r] >= 0;
-        MassAcc<S, C> rs = MassAcc<S, C>(er[r]);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) rs += MassAcc<S, C>(f[r][i]);
         const C* R = s_rho + (ly + r * LY + HC) * RX + lx + HC;
         const C* U = s_mu + (ly + r * LY + 2) * MX + lx + 2;
         const C rr = R[0];
@@ -478,9 +494,9 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
         const C Fy = -rr * cd1(U[-2 * MX], U[-MX], U[MX], U[2 * MX]) + cd1(R[-2 * RX], R[-RX], R[RX], R[2 * RX]) / C(3);
         C out[9];
         C rho, dux, duy, sx2, sy2, duu15;
-        collide9<S, C, MRT>(a, coll, f[r], rs, coll ? Fx : C(0), coll ? Fy : C(0), out, rho, dux, duy, sx2, sy2, duu15);
+        collide9<S, C, MRT>(a, coll, f[r], rs[r], coll ? Fx : C(0), coll ? Fy : C(0), out, rho, dux, duy, sx2, sy2, duu15);
         const uint32_t x = uint32_t(y0 + ly + r * LY) * uint32_t(nx) + uint32_t(x0 + lx);
-        store_node<S, C>(rfb, rout, ns, out_node ? x * s : OOB, coll, tg[r], out, rho, dux, duy, sx2, sy2,
+        store_node<S, C>(p.nt, rfb, rout, ns, out_node ? x * s : OOB, coll, tg[r], out, rho, dux, duy, sx2, sy2,
                          duu15, ds[r]);
     }
     if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
@@ -491,6 +507,16 @@ hipError_t launch_cptile(mcb_ctx* c, const void* fcur, const void* rcur, void* f
     constexpr int TY = NT / TX * RPL;
     ArgsCP<S, C> p = cp_args<S, C>(c, fcur, rcur, fnext, rnext);
     p.a.nsx = (p.a.nx + TX - 1) / TX;
+    // Panels of 16 tiles: 4096^2 FP32 482 -> 451 us (1.16 -> 0.94 GB read), FP64 948 -> 872; 8, 32 and 64
+    // tiles 472, 458 and 478; no difference at 3000 x 2900.  Non-temporal stores once the lattices outgrow
+    // the memory-side cache, where they keep the lattice being read in it: 4096^2 FP32 451 -> 435, FP64
+    // 872 -> 847, 2560 x 2500 FP32 187 -> 179, FP64 1400 x 1300 (262 MB) 112 -> 105; below it they cost up
+    // to a third (1800 x 1500 FP32 60 -> 82).  A tile row of FP32 is one cache line, written in two
+    // parts where the rows of the lattice are not whole lines: there they are no gain (3000 x 2900
+    // 260 -> 283, 3600 x 3500 364 -> 366, 2000 x 1850 112 -> 107).
+    p.a.H = 16;
+    const int64_t bytes = 2 * state_bytes(c->p.precision, 9, c->g.N);
+    p.nt = bytes > (int64_t(1) << 28) && (sizeof(S) == 8 || (p.a.nx * int(sizeof(S))) % 128 == 0);
     p.a.nblocks = p.a.nsx * ((p.a.ny + TY - 1) / TY);
     const bool mrt = c->p.collision == MCB_COLL_MRT;
     const auto k = pull ? (mrt ? k_cptile<S, C, TX, NT, RPL, WPE, true, true> : k_cptile<S, C, TX, NT, RPL, WPE, true, false>)
@@ -502,8 +528,9 @@ hipError_t launch_cptile(mcb_ctx* c, const void* fcur, const void* rcur, void* f
 // 32 x 32 tiles of two nodes a lane pull 0.9 ring nodes per node, 32 x 16 tiles of one node a lane 1.4, but
 // run a shorter chain; the larger ones are taken once the box holds two of them per compute unit
 // (1024^2 FP64 58 us against 62, 2048 x 1024 FP32 52 against 56, 4096^2 FP32 480 against 534; 512^2 FP64,
-// one a unit, 24 against 21, 724^2 42 against 38).  FP32 arithmetic fits 80 VGPRs, six waves per
-// SIMD; FP64 is held to 128 (a 36-byte spill): unbounded, at three waves, 1024^2 took 78 us against 60.
+// one a unit, 24 against 21, 724^2 42 against 38; panels and streaming stores came after).  FP32 arithmetic
+// fits 80 VGPRs, six waves per SIMD; FP64 is held to 128 (a 28-byte spill): unbounded, at three waves,
+// 1024^2 took 78 us against 60.
 template <class S, class C>
 hipError_t cptile_t(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
     constexpr int WPE = sizeof(C) == 8 ? 4 : 6;
