@@ -286,6 +286,7 @@ mcb_status mcb_create(const mcb_params* params, mcb_ctx** out) {
     c->g.Q = c->p.dim == 2 ? 9 : 19;
     c->g.N = int64_t(c->p.nx) * c->p.ny * c->p.nz;
     c->L = make_layout(c->p, 0, 0, 0, 0);
+    download_open();
     *out = c;
     return MCB_OK;
 }
@@ -295,6 +296,7 @@ void mcb_destroy(mcb_ctx* c) {
     if (c->ev_made)
         for (int r = 0; r < mcb_ctx::RING; ++r)
             for (int k = 0; k < 2; ++k) (void)hipEventDestroy(c->ev[r][k]);
+    download_close();
     delete c;
 }
 
@@ -548,8 +550,7 @@ mcb_status mcb_get_f(mcb_ctx* c, double* f) {
     const char* cur = static_cast<const char*>(fcur(c));
     for (int i = 0; i < c->g.Q; ++i) {
         HIPCHK(convert_plane_out(c, cur + plane_bytes_off(c->p.precision, i, c->g.N), stage_buf, i));
-        HIPCHK(hipMemcpyAsync(f + i * c->g.N, stage_buf, 8 * c->g.N, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
+        HIPCHK(download(c, f + i * c->g.N, stage_buf, 8 * c->g.N));
     }
     return check_flags(c, nullptr);
 }

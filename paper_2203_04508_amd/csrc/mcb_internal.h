@@ -190,6 +190,12 @@ hipError_t adj_step2d(mcb_ctx* c, const AdjWork& w, const void* gt, const void* 
                       const double* lamR1, double* lam0, double* lamR0);
 hipError_t adj_loss(mcb_ctx* c, const AdjWork& w, const void* g, int kind, const double* prm, double dloss, double* lam);
 
+// download.hip: copies n bytes of device memory to pageable host memory after what the stream holds, and
+// waits for it.  download_open / download_close: a context comes, goes
+hipError_t download(mcb_ctx* c, void* dst, const void* src, int64_t n);
+void download_open();
+void download_close();
+
 // monitor.hip
 // partials (MON_BLOCKS x MON_FIELDS doubles) and result (MON_FIELDS doubles): null = the context's
 // lattice arena

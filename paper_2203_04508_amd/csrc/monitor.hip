@@ -678,11 +678,11 @@ hipError_t moments_t(mcb_ctx* c, const void* fcur, double* rho, double* v) {
     hipError_t e = moments_dev<S, C>(c, fcur);
     if (e != hipSuccess) return e;
     if (rho) {
-        e = hipMemcpyAsync(rho, sr, sizeof(double) * c->g.N, hipMemcpyDeviceToHost, c->stream);
+        e = download(c, rho, sr, int64_t(sizeof(double)) * c->g.N);
         if (e != hipSuccess) return e;
     }
     if (v) {
-        e = hipMemcpyAsync(v, sv, sizeof(double) * c->g.N * c->g.dim, hipMemcpyDeviceToHost, c->stream);
+        e = download(c, v, sv, int64_t(sizeof(double)) * c->g.N * c->g.dim);
         if (e != hipSuccess) return e;
     }
     return hipStreamSynchronize(c->stream);

@@ -17,6 +17,10 @@ BC = {"present": 0, "ibc": 1, "mibc": 2, "hbbc": 3}
 
 @pytest.fixture(scope="module")
 def mcb():
+    import torch  # before the library: both use the HIP runtime that torch brings
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
     from paper_2203_04508_amd import mcb as m
 
     m.load()
