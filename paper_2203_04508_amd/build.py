@@ -9,7 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmcb.so")
 CEILING = os.path.join(HERE, "mcb_ceiling")  # standalone copy / plain-pull bandwidth probe
-SOURCES = ["api.hip", "geometry.hip", "step2d.hip", "tile2d.hip", "step3d.hip", "flat3d.hip", "monitor.hip", "download.hip", "adjoint.hip", "adjoint2d.hip"]
+SOURCES = ["api.hip", "geometry.hip", "step2d.hip", "tile2d.hip", "step3d.hip", "flat3d.hip", "monitor.hip",
+           "download.hip", "adjoint.hip", "adjoint2d.hip", "adjoint3d.hip"]
 ARCH = os.environ.get("MCB_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [

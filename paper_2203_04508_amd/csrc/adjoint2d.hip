@@ -31,17 +31,6 @@ __device__ __forceinline__ void eadd(int i, double v, double (&acc)[2]) {
     if (kEy[i] != 0) acc[1] += kEy[i] > 0 ? v : -v;
 }
 
-// the value at a byte offset below 4 GiB from a uniform base (the address is a scalar base and a 32-bit
-// lane offset; an array of one double per node stays below 4 GiB, since a population lattice does)
-template <class T>
-__device__ __forceinline__ T ldo(const T* base, uint32_t off) {
-    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + off);
-}
-template <class T>
-__device__ __forceinline__ void sto(T* base, uint32_t off, T v) {
-    *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off) = v;
-}
-
 // periodic image of a coordinate
 __device__ __forceinline__ int image(int v, int m) {
     while (v < 0) v += m;

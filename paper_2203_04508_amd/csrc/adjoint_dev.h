@@ -1,5 +1,5 @@
-// Device data and helpers of the reverse mode, shared by the pass kernels (adjoint.hip) and the D2Q9 tile
-// kernels (adjoint2d.hip).
+// Device data and helpers of the reverse mode, shared by the loss kernels (adjoint.hip), the D2Q9 tile
+// kernels (adjoint2d.hip) and the D3Q19 kernels (adjoint3d.hip).
 #pragma once
 
 #include "kernels_common.h"
@@ -16,20 +16,6 @@ __device__ inline C wgt(int L, int i) {
 __device__ inline double wforce(int L, int i) {
     if (L == 0) return i < 5 ? 1.0 / 3.0 : 1.0 / 12.0;
     return i < 7 ? 1.0 / 6.0 : 1.0 / 12.0;
-}
-
-// a node's lattice position (32-bit arithmetic: N < 2^31) and its periodic neighbours
-struct Pos {
-    int x, y, z;
-};
-__device__ inline Pos pos_of(const GridDev& g, int64_t x) {
-    const uint32_t u = uint32_t(x), nx = uint32_t(g.nx), nxy = nx * uint32_t(g.ny);
-    const uint32_t z = u / nxy, r = u - z * nxy, y = r / nx;
-    return {int(r - y * nx), int(y), int(z)};
-}
-__device__ inline int64_t nbr_at(const GridDev& g, int L, const Pos& p, int i, int sign) {
-    return int64_t(wrap1(p.x + sign * c_ex[L][i], g.nx)) +
-           int64_t(g.nx) * (wrap1(p.y + sign * c_ey[L][i], g.ny) + int64_t(g.ny) * wrap1(p.z + sign * c_ez[L][i], g.nz));
 }
 
 // opposite direction, a compile-time constant inside unrolled loops (D2Q9 pairs 1-3, 2-4, 5-7, 6-8;
@@ -70,18 +56,10 @@ __device__ constexpr int kM2[9][9] = {{1, 1, 1, 1, 1, 1, 1, 1, 1},     {-4, -1, 
                                       {0, 0, -2, 0, 2, 1, 1, -1, -1},   {0, 1, -1, 1, -1, 0, 0, 0, 0},
                                       {0, 0, 0, 0, 0, 1, -1, 1, -1}};
 
-// boundary index of a boundary node's tag
-__device__ inline int64_t bidx(const AdjDev& A, int tg) { return A.L == 0 ? int64_t(tg >> 8) : int64_t(tg - 1); }
-
-// link bits (bit j-1: x + e_j solid) of a fluid node, and the record slot of its link j
+// link bits (bit j-1: x + e_j solid) of a fluid node
 __device__ inline uint32_t link_bits(const AdjDev& A, int64_t x, int tg) {
     if (tg <= 0) return 0u;
     return A.L == 0 ? uint32_t(tg) & 0xFFu : A.nmask[x];
-}
-__device__ inline int64_t link_slot(const AdjDev& A, int tg, uint32_t mask, int j) {
-    (void)mask;
-    if (A.L == 0) return int64_t(tg >> 8) * Q2_LINKS + (j - 1);
-    return int64_t(tg - 1) * Q3_LINKS + (j - 1);
 }
 
 // psi(rho) = sqrt(2 (p - rho/3) / G), p the Carnahan-Starling pressure, and d psi / d rho
@@ -104,6 +82,17 @@ __device__ inline double ldf(const S* g, const AdjDev& A, int i, int64_t x) {
 template <>
 __device__ inline double ldf<double>(const double* g, const AdjDev& A, int i, int64_t x) {
     return g[i * A.g.N + x] + wgt<double>(A.L, i) * A.rho_ref;
+}
+
+// the value at a byte offset below 4 GiB from a uniform base (the address is a scalar base and a 32-bit
+// lane offset; an array of one double per node stays below 4 GiB, since a population lattice does)
+template <class T>
+__device__ __forceinline__ T ldo(const T* base, uint32_t off) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + off);
+}
+template <class T>
+__device__ __forceinline__ void sto(T* base, uint32_t off, T v) {
+    *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off) = v;
 }
 
 AdjDev make_dev(const mcb_ctx* c) {

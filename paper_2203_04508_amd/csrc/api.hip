@@ -94,16 +94,19 @@ AdjPlan adj_plan(const mcb_ctx* c, int64_t nsteps, int64_t k) {
         a.lam[b] = take(8 * Q * N);
         a.lamR[b] = take(8 * (a.nslots > 0 ? a.nslots : 1));
     }
-    a.p = take(8 * Q * N);
     a.pbar = take(8 * Q * N);
     a.rho = take(8 * N);
     a.psi = take(8 * N);
     a.dpsi = take(8 * N);
     a.rave = take(8 * N);
     a.den = take(8 * N);
-    a.rbar = take(8 * N);
-    a.qbar = take(8 * N);
     a.Fbar = take(8 * 3 * N);
+    if (c->g.dim == 3) {
+        a.mom = take(8 * 3 * N);
+        a.own = take(8 * N);
+        a.rbar = take(8 * N);
+        a.qbar = take(8 * N);
+    }
     a.dphi = take(8 * (c->n_wall > 0 ? c->n_wall : 1));
     a.part = take(8 * 2 * MON_BLOCKS);
     a.sums = take(8 * 2);
@@ -596,7 +599,6 @@ static AdjWork adj_work(mcb_ctx* c) {
     auto d = [&](int64_t off) { return reinterpret_cast<double*>(c->adj + off); };
     AdjWork w;
     w.rho0 = d(a.rho0);
-    w.p = d(a.p);
     w.pbar = d(a.pbar);
     w.rho = d(a.rho);
     w.psi = d(a.psi);
@@ -606,6 +608,8 @@ static AdjWork adj_work(mcb_ctx* c) {
     w.rbar = d(a.rbar);
     w.qbar = d(a.qbar);
     w.Fbar = d(a.Fbar);
+    w.mom = d(a.mom);
+    w.own = d(a.own);
     w.dphi = d(a.dphi);
     w.part = d(a.part);
     w.sums = d(a.sums);

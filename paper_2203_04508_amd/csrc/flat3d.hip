@@ -31,53 +31,13 @@ struct Flat3 {
     int64_t n_wall;
 };
 
-// The node of a lane and the byte offsets of its neighbours x + e_i in an array of T, from one scalar
-// division per workgroup: the lanes of a workgroup take NT consecutive nodes of the lattice.
-struct Node3 {
-    uint32_t node;
-    bool on;
-    int x, y, z;
-};
-__device__ __forceinline__ Node3 node3(int nx, int ny, int nz) {
-    const uint32_t n0 = uint32_t(blockIdx.x) * NT, t = threadIdx.x;
-    const uint32_t nxy = uint32_t(nx) * uint32_t(ny), N = nxy * uint32_t(nz);
-    Node3 r;
-    const uint32_t z0 = n0 / nxy, y0 = (n0 - z0 * nxy) / uint32_t(nx);
-    r.node = n0 + t;
-    r.on = r.node < N;
-    r.x = int(n0 - z0 * nxy - y0 * uint32_t(nx) + t);
-    r.y = int(y0);
-    r.z = int(z0);
-    while (r.x >= nx) {
-        r.x -= nx;
-        ++r.y;
-    }
-    while (r.y >= ny) {
-        r.y -= ny;
-        ++r.z;
-    }
-    if (!r.on) r.node = 0, r.x = r.y = r.z = 0;
-    return r;
-}
-template <class T>
-__device__ __forceinline__ void neighbours(const Node3& p, int nx, int ny, int nz, uint32_t (&off)[19]) {
-    constexpr uint32_t s = sizeof(T);
-    const uint32_t row = uint32_t(nx) * s, pl = row * uint32_t(ny), o = p.node * s;
-    const uint32_t xo[3] = {p.x == 0 ? row - s : 0u - s, 0u, p.x == nx - 1 ? s - row : s};
-    const uint32_t yo[3] = {o + (p.y == 0 ? pl - row : 0u - row), o, o + (p.y == ny - 1 ? row - pl : row)};
-    const uint32_t zo[3] = {p.z == 0 ? pl * uint32_t(nz - 1) : 0u - pl, 0u, p.z == nz - 1 ? 0u - pl * uint32_t(nz - 1) : pl};
-#pragma unroll
-    for (int i = 0; i < 19; ++i) off[i] = yo[kEy3[i] + 1] + xo[kEx3[i] + 1] + zo[kEz3[i] + 1];
-}
-__device__ constexpr int opp3(int i) { return i == 0 ? 0 : ((i & 1) ? i + 1 : i - 1); }
-
 template <class S, class C, bool PULL, bool IBC>
 __global__ __launch_bounds__(NT) void k_rho3f(Flat3<S, C> p) {
     const Args3<S, C>& a = p.a;
     constexpr uint32_t s = sizeof(S);
     const uint32_t N = uint32_t(a.nx) * uint32_t(a.ny) * uint32_t(a.nz), ns = N * s;
     const __amdgpu_buffer_rsrc_t fa = make_res(a.fa, uint64_t(19) * ns);
-    const Node3 q = node3(a.nx, a.ny, a.nz);
+    const Node3 q = node3<NT>(a.nx, a.ny, a.nz);
     const int tg = a.tag[q.node];
     uint32_t off[19];
     neighbours<S>(q, a.nx, a.ny, a.nz, off);
@@ -153,7 +113,7 @@ __global__ __launch_bounds__(NT, sizeof(C) == 8 ? 2 : 4) void k_collide3f(Flat3<
     const __amdgpu_buffer_rsrc_t rin = make_res(a.rin, uint64_t(a.n_bnodes) * REC3 * sc);
     const __amdgpu_buffer_rsrc_t rout = make_res(a.rout, uint64_t(a.n_bnodes) * REC3 * sc);
     const __amdgpu_buffer_rsrc_t rla = make_res(a.la, uint64_t(a.n_bnodes) * Q3_LINKS * sc);
-    const Node3 q = node3(a.nx, a.ny, a.nz);
+    const Node3 q = node3<NT>(a.nx, a.ny, a.nz);
     const int tg = a.tag[q.node];
     uint32_t off[19];
     neighbours<S>(q, a.nx, a.ny, a.nz, off);

@@ -81,13 +81,13 @@ Layout make_layout(const mcb_params& p, int64_t n_shapes, int64_t n_links, int64
 struct AdjPlan {
     int64_t nsteps, k, nck, state_b, rec_b, nslots;
     int64_t rho0, ck, ck_rec, seg, seg_rec, lam[2], lamR[2];
-    int64_t p, pbar, rho, psi, dpsi, rave, den, rbar, qbar, Fbar, dphi, part, sums, bytes;
+    int64_t mom, pbar, rho, psi, dpsi, rave, den, rbar, qbar, Fbar, own, dphi, part, sums, bytes;
 };
 
 // device pointers of the work arrays
 struct AdjWork {
     const double* rho0;
-    double *p, *pbar, *rho, *psi, *dpsi, *rave, *den, *rbar, *qbar, *Fbar, *dphi, *part, *sums;
+    double *mom, *pbar, *rho, *psi, *dpsi, *rave, *den, *rbar, *qbar, *Fbar, *own, *dphi, *part, *sums;
 };
 int64_t storage_bytes(int precision);
 // bytes of one population state (Q planes; FP16 storage keeps plane 0 in FP32) and the byte offset
@@ -185,8 +185,10 @@ hipError_t init_feq(mcb_ctx* c, const double* rho, const double* u, void* fout);
 // loss of a state with (lam != nullptr) its gradient lam = dloss * d loss / d g
 hipError_t adj_step(mcb_ctx* c, const AdjWork& w, const void* gt, const void* rec, int pull, const double* lam1,
                     const double* lamR1, double* lam0, double* lamR0);
-// adjoint2d.hip: the transposed D2Q9 step
+// adjoint2d.hip, adjoint3d.hip: the transposed step of each lattice
 hipError_t adj_step2d(mcb_ctx* c, const AdjWork& w, const void* gt, const void* rec, int pull, const double* lam1,
+                      const double* lamR1, double* lam0, double* lamR0);
+hipError_t adj_step3d(mcb_ctx* c, const AdjWork& w, const void* gt, const void* rec, int pull, const double* lam1,
                       const double* lamR1, double* lam0, double* lamR0);
 hipError_t adj_loss(mcb_ctx* c, const AdjWork& w, const void* g, int kind, const double* prm, double dloss, double* lam);
 

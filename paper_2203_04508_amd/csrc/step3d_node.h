@@ -31,6 +31,48 @@ __device__ __forceinline__ C edot3(int ex, int ey, int ez, C x, C y, C z) {
     return ez == 0 ? a : ((ex == 0 && ey == 0) ? tz : a + tz);
 }
 
+// One lane per node, NT consecutive nodes of the lattice per workgroup: the node of a lane (one scalar
+// division per workgroup; lanes past the last node repeat node 0) and the byte offsets of its
+// neighbours x + e_i in an array of T.
+struct Node3 {
+    uint32_t node;
+    bool on;
+    int x, y, z;
+};
+template <int NT>
+__device__ __forceinline__ Node3 node3(int nx, int ny, int nz) {
+    const uint32_t n0 = uint32_t(blockIdx.x) * NT, t = threadIdx.x;
+    const uint32_t nxy = uint32_t(nx) * uint32_t(ny), N = nxy * uint32_t(nz);
+    Node3 r;
+    const uint32_t z0 = n0 / nxy, y0 = (n0 - z0 * nxy) / uint32_t(nx);
+    r.node = n0 + t;
+    r.on = r.node < N;
+    r.x = int(n0 - z0 * nxy - y0 * uint32_t(nx) + t);
+    r.y = int(y0);
+    r.z = int(z0);
+    while (r.x >= nx) {
+        r.x -= nx;
+        ++r.y;
+    }
+    while (r.y >= ny) {
+        r.y -= ny;
+        ++r.z;
+    }
+    if (!r.on) r.node = 0, r.x = r.y = r.z = 0;
+    return r;
+}
+template <class T>
+__device__ __forceinline__ void neighbours(const Node3& p, int nx, int ny, int nz, uint32_t (&off)[19]) {
+    constexpr uint32_t s = sizeof(T);
+    const uint32_t row = uint32_t(nx) * s, pl = row * uint32_t(ny), o = p.node * s;
+    const uint32_t xo[3] = {p.x == 0 ? row - s : 0u - s, 0u, p.x == nx - 1 ? s - row : s};
+    const uint32_t yo[3] = {o + (p.y == 0 ? pl - row : 0u - row), o, o + (p.y == ny - 1 ? row - pl : row)};
+    const uint32_t zo[3] = {p.z == 0 ? pl * uint32_t(nz - 1) : 0u - pl, 0u, p.z == nz - 1 ? 0u - pl * uint32_t(nz - 1) : pl};
+#pragma unroll
+    for (int i = 0; i < 19; ++i) off[i] = yo[kEy3[i] + 1] + xo[kEx3[i] + 1] + zo[kEz3[i] + 1];
+}
+__device__ constexpr int opp3(int i) { return i == 0 ? 0 : ((i & 1) ? i + 1 : i - 1); }
+
 template <class S, class C>
 struct RhoArgs {
     const S* fa;                 // post-collision populations of time t, SoA [19][N]
