@@ -1,15 +1,19 @@
-// Transposed D2Q9 step in two tile kernels (the map and its transposes are written out in adjoint.hip,
-// whose pass kernels serve D3Q19).
+// Transposed D2Q9 step in two tile kernels (the map and its transposes are written out in adjoint.hip).
 //
 // Why tiles.  One pass per transpose writes and reads every intermediate (p, rho, psi, pbar twice, F,
 // rhobar, qbar) through memory: about 900 bytes per node and six launches of 5 to 17 us each at 512^2
 // (eleven with the chemical-potential model), where the arrays live in the memory-side cache and each
 // launch is bound by one round trip per dependent load.  Here the intermediates of a tile stay in LDS
 // and registers, and only pbar, Fbar and the fields they belong to go from the first kernel to the
-// second.  A reverse step at 512^2 FP32 storage: 65 -> 29 us (15.3 the first kernel, 4.2 TB/s of what it
-// reads and writes, 13.8 the second, 4.0 TB/s); at 301 x 203 FP64 in the chemical-potential model
-// 77 -> 25 us.  Tiles of 32 x 16 instead of 32 x 8 for the pseudopotential kernels measured the same
-// (15.6 and 14.3 us); lambda loaded before the links instead of after spills 96 bytes a lane (22.7 us).
+// second.  A reverse step at 512^2 FP32 storage: 65 -> 25 us (14.3 the first kernel, 4.2 TB/s of what it
+// reads and writes, 10.6 the second); at 301 x 203 FP64 in the chemical-potential model 77 -> 23 us.
+// Tiles of 32 x 16 instead of 32 x 8 for the pseudopotential kernels measured the same (15.6 and 14.3
+// us); lambda loaded before the links instead of after spills 96 bytes a lane (22.7 us).
+//
+// The grid of a middle-sized box is one round, so a kernel lasts as long as its slowest wave, one with
+// boundary nodes: the links take their coefficients, records and adjoints as whole vectors, one
+// round trip after the tag (a load per link, each behind its branch: 15.3 and 13.8 us), and the eq. 16
+// share of a neighbour is added to pbar by the first kernel, at its own node.
 #include "adjoint_dev.h"
 
 namespace mcb {
@@ -58,8 +62,9 @@ __device__ __forceinline__ void ring_at(int j, int& rx, int& ry) {
     rx = q < 0 ? j % RX : (q % (2 * H) < H ? q % (2 * H) : TX + q % (2 * H));
 }
 
-// populations of node (cx, cy) of a state, pulled (eq. 5: from x - e_i) or its own
-template <class S, bool PULL>
+// populations arriving at node (cx, cy) of a state (eq. 5, from x - e_i), as stored: less w rho_ref, which drops
+// out of the links and the momentum
+template <class S>
 __device__ __forceinline__ void pops(const AdjDev& A, const S* __restrict__ g, int cx, int cy, double (&f)[9]) {
     const int nx = A.g.nx, ny = A.g.ny;
     const uint32_t xo[3] = {uint32_t(cx == nx - 1 ? 0 : cx + 1), uint32_t(cx), uint32_t(cx == 0 ? nx - 1 : cx - 1)};
@@ -67,83 +72,98 @@ __device__ __forceinline__ void pops(const AdjDev& A, const S* __restrict__ g, i
                             uint32_t(cy == 0 ? ny - 1 : cy - 1) * uint32_t(nx)};
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        const uint32_t x = PULL ? xo[kEx[i] + 1] + yo[kEy[i] + 1] : xo[1] + yo[1];
+        const uint32_t x = xo[kEx[i] + 1] + yo[kEy[i] + 1];
         if (kMixed<S> && i == 0)
-            f[0] = double(ldo(reinterpret_cast<const float*>(g), x * 4u));  // FP16 storage: in FP32
+            f[i] = double(ldo(reinterpret_cast<const float*>(g), x * 4u));  // FP16 storage: in FP32
         else
             f[i] = double(ldo(g + plane_off<S>(i, A.g.N), x * uint32_t(sizeof(S))));
-        f[i] += wgt<double>(0, i) * A.rho_ref;
     }
 }
 
-// Links of boundary node (cx, cy) (tag tg > 0) on its pulled populations v: v becomes the
-// pre-collision populations (eqs. 16-18).  FULL = false forms only their sum right, which where eq. 18
-// applies takes the node's own population on each link in place of f_in and no correction.
-template <class S, class RC, bool FULL>
-__device__ __forceinline__ void links_on(const AdjDev& A, const S* __restrict__ g, const RC* __restrict__ la,
-                                         const RC* __restrict__ rec, int tg, int cx, int cy, double (&v)[9]) {
-    double fo[9];
-    pops<S, false>(A, g, cx, cy, fo);
-    const int64_t b = tg >> 8;
-    double r0 = 0.0, m1[2] = {0, 0}, F0[2] = {0, 0};
-    if (FULL) {
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            r0 += fo[i];
-            eadd(i, fo[i], m1);
-        }
-        // F = rho du from the forcing terms at the head of the boundary record
-        for (int k = 0; k < 2; ++k) F0[k] = double(rec[b * A.fs]) * double(rec[b * A.fs + 1 + k]);
-    }
-    const double m0[2] = {m1[0] - F0[0], m1[1] - F0[1]};
-    const double mm0 = m0[0] * m0[0] + m0[1] * m0[1], mm1 = m1[0] * m1[0] + m1[1] * m1[1];
-    double dm = 0.0, pl[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) pl[i] = v[i];
+// link coefficients of a boundary node (NO_LINK: none)
+template <class RC>
+__device__ __forceinline__ void coefs(const AdjDev& A, const RC* __restrict__ la, int tg, RC (&a)[Q2_LINKS]) {
+    ld_vec(make_res(la, uint64_t(A.nb) * Q2_LINKS * sizeof(RC)), uint32_t(tg >> 8) * uint32_t(Q2_LINKS * sizeof(RC)), a);
+}
+
+// Links of a boundary node (tag tg > 0) on its pulled populations v: v becomes the pre-collision populations
+// (eqs. 16-18).  All from its record: rho, du = F / rho, 2u + du, 1.5 du.(2u + du) and the node's own
+// populations.
+template <class RC>
+__device__ __forceinline__ void links_on(const AdjDev& A, const RC* __restrict__ la, const RC* __restrict__ rec, int tg,
+                                         double (&v)[9]) {
+    RC h[RF2 + 8], a[Q2_LINKS];
+    ld_vec(make_res(rec, uint64_t(A.nb) * REC2 * sizeof(RC)), uint32_t(tg >> 8) * uint32_t(REC2 * sizeof(RC)), h);
+    coefs(A, la, tg, a);
+    const double kr = A.kF * double(h[0]), dx = double(h[1]), dy = double(h[2]), sx = double(h[3]), sy = double(h[4]);
+    const double duu = double(h[5]);
+    double dm = 0.0;
+    // a slot that a link replaces is never one that an eq. 16 link reads (its x2 = x - e_j is fluid)
 #pragma unroll
     for (int j = 1; j < 9; ++j) {
         const bool lk = (tg >> (j - 1)) & 1;
-        double B = fo[j];
-        if (FULL) {
-            const double a = lk ? double(la[b * Q2_LINKS + (j - 1)]) : 1.0;
-            // R_j = E_j(rho, m + F) - E_j(rho, m), E the equilibrium in momentum form
-            const double em0 = edot(j, m0[0], m0[1]), em1 = edot(j, m1[0], m1[1]);
-            const double Fj =
-                wgt<double>(0, j) * (3.0 * (em1 - em0) + (4.5 * (em1 * em1 - em0 * em0) - 1.5 * (mm1 - mm0)) / r0);
-            // x2 = x - e_j: its value is the one pulled into direction j (not used where x2 is solid: a = 1)
-            const double c1 = fabs(a), c2 = 1.0 - c1;
-            const double o = a < 0.0 ? fo[opp<0>(j)] : (c2 != 0.0 ? pl[j] : 0.0);
-            B = c1 * fo[j] + c2 * (o + A.kF * Fj);
-            dm += lk ? fo[j] - B : 0.0;
-        }
+        const double aj = double(a[j - 1]), c1 = fabs(aj), c2 = 1.0 - c1, fj = double(h[RF2 + j - 1]);
+        const double ed = edot(j, dx, dy), es = edot(j, sx, sy);
+        const double F = wgt<double>(0, j) * kr * (3.0 * ed + 4.5 * ed * es - duu);
+        const double o = c2 != 0.0 ? (aj < 0.0 ? double(h[RF2 + opp<0>(j) - 1]) : v[j]) : 0.0;
+        const double B = c1 * fj + c2 * (o + F);
         v[opp<0>(j)] = lk ? B : v[opp<0>(j)];
+        dm += lk ? fj - B : 0.0;
     }
     v[0] += A.k18 * dm;
+}
+
+__device__ __forceinline__ double sum9(const AdjDev& A, const double (&v)[9]) {
+    double r = A.rho_ref;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) r += v[i];
+    return r;
 }
 
 // density of node (cx, cy) after the pull
 template <class S, class RC>
 __device__ __forceinline__ double density(const AdjDev& A, const S* __restrict__ g, const RC* __restrict__ la,
                                           const RC* __restrict__ rec, int tg, int cx, int cy) {
-    double w[9], r = 0.0;
-    pops<S, true>(A, g, cx, cy, w);
+    double w[9];
+    pops<S>(A, g, cx, cy, w);
     if (tg > 0) {
-        if (A.k18 != 0.0)
-            links_on<S, RC, false>(A, g, la, rec, tg, cx, cy, w);
-        else
-            links_on<S, RC, true>(A, g, la, rec, tg, cx, cy, w);
-    }
+        if (A.k18 != 0.0) {
+            // where eq. 18 applies, the node's own population on each link takes the place of f_in (its slot
+            // was pulled from a solid node and holds 0)
+            constexpr int B = int(RF2 * sizeof(RC)) & ~15, K = B / int(sizeof(RC));
+            RC h[RF2 + 8 - K];
+            ld_vec(make_res(rec, uint64_t(A.nb) * REC2 * sizeof(RC)), uint32_t(tg >> 8) * uint32_t(REC2 * sizeof(RC)) + B, h);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) r += w[i];
-    return r;
+            for (int j = 1; j < 9; ++j) w[0] += ((tg >> (j - 1)) & 1) ? double(h[RF2 - K + j - 1]) : 0.0;
+        } else {
+            links_on<RC>(A, la, rec, tg, w);
+        }
+    }
+    return sum9(A, w);
 }
 
 // Transposed collision of a fluid node (tag tg) with density r, momentum j and force F: from
 // lam = lambda(t + 1) and the adjoints lamR1 of its links' forcing terms, the adjoint pb of p through
-// the direct and the (rho, j) dependences, and Fb of F.
-__device__ __forceinline__ void collide_T9(const AdjDev& A, double r, const double (&j)[2], const double (&F)[2],
-                                           const double (&lam)[9], int tg, const double* __restrict__ lamR1, double (&pb)[9],
-                                           double (&Fb)[2]) {
+// the direct and the (rho, j) dependences, and Fb of F.  A link (x, i) of eq. 16 uses o = f_i(x - e_i), which x
+// also pulls in direction i, so pb_i takes c2 Bbar_i(x) here, less its density part (no other link of x reads
+// that pb_i: x - e_i is fluid).
+template <class RC>
+__device__ __forceinline__ void collide_T9(const AdjDev& A, const RC* __restrict__ la, double r, const double (&j)[2],
+                                           const double (&F)[2], const double (&lam)[9], int tg,
+                                           const double* __restrict__ lamR1, double (&pb)[9], double (&Fb)[2]) {
+    double rr[Q2_LINKS];  // adjoint of the forcing term on each link (0 without a link)
+    RC a[Q2_LINKS];
+#pragma unroll
+    for (int i = 0; i < Q2_LINKS; ++i) {
+        rr[i] = 0.0;
+        a[i] = RC(NO_LINK);
+    }
+    if (tg > 0) {
+        ld_vec(make_res(lamR1, uint64_t(A.nb) * Q2_LINKS * 8u), uint32_t(tg >> 8) * (Q2_LINKS * 8u), rr);
+        coefs(A, la, tg, a);
+#pragma unroll
+        for (int i = 0; i < Q2_LINKS; ++i) rr[i] = ((tg >> i) & 1) ? rr[i] : 0.0;
+    }
     // lt = (I - K)^T lambda: the adjoint of the direct dependence on p
     double lt[9];
     if (A.mrt) {
@@ -170,22 +190,18 @@ __device__ __forceinline__ void collide_T9(const AdjDev& A, double r, const doub
     }
     const double m1[2] = {j[0] + F[0], j[1] + F[1]};
     const double mm0 = j[0] * j[0] + j[1] * j[1], mm1 = m1[0] * m1[0] + m1[1] * m1[1];
-    const uint32_t msk = tg > 0 ? uint32_t(tg) & 0xFFu : 0u;
     const double ir = 1.0 / r, ir2 = ir * ir;
     // al: adjoint of E_i(rho, j + F); be: of E_i(rho, j), (K - I)^T lambda (both with the weight w_i).
     // Opposite directions share (e.m)^2 and have opposite e.m, so each pair enters by its sum and
     // difference.
     double sa = 0.0, sb = 0.0, qa = 0.0, d1[2] = {0, 0}, d0[2] = {0, 0};
-    auto link_adj = [&](int i) {  // adjoint of the forcing term on the node's link in direction i
-        return ((msk >> (i - 1)) & 1u) ? ldo(lamR1, (uint32_t(tg >> 8) * Q2_LINKS + uint32_t(i - 1)) * 8u) : 0.0;
-    };
     sa = wgt<double>(0, 0) * lam[0];
     sb = -wgt<double>(0, 0) * lt[0];
     constexpr int pairs[4] = {1, 2, 5, 6};
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const int i = pairs[p], o = opp<0>(i);
-        const double w = wgt<double>(0, i), ri = link_adj(i), ro = link_adj(o);
+        const double w = wgt<double>(0, i), ri = rr[i - 1], ro = rr[o - 1];
         const double ai = lam[i] + ri, ao = lam[o] + ro, bi = lt[i] + ri, bo = lt[o] + ro;
         const double ap = w * (ai + ao), am = w * (ai - ao), bp = -w * (bi + bo), bm = -w * (bi - bo);
         const double em0 = edot(i, j[0], j[1]), em1 = edot(i, m1[0], m1[1]);
@@ -208,50 +224,62 @@ __device__ __forceinline__ void collide_T9(const AdjDev& A, double r, const doub
     rb += Fb[0] * A.grav[0] + Fb[1] * A.grav[1];
 #pragma unroll
     for (int i = 0; i < 9; ++i) pb[i] = lt[i] + rb + (i == 0 ? 0.0 : edot(i, jb[0], jb[1]));
-}
-
-// Transposed streaming, links and eq. 18 at a node (tag tg): lambda(t) and lambda_R(t) from pbar of the
-// node (pby) and of its neighbours x + e_i in direction i (pxi), without the density adjoint, which rb
-// holds around the node (row stride rs); tag_at(i): the tag of x + e_i.
-template <class RC, class TagAt>
-__device__ __forceinline__ void stream_T9(const AdjDev& A, const RC* __restrict__ la, const double* __restrict__ pbar, int tg,
-                                          const uint32_t (&xo)[3], const uint32_t (&yo)[3], double (&pby)[9],
-                                          const double (&pxi)[9], const double* rb, int rs, TagAt tag_at,
-                                          double* __restrict__ lam0, double* __restrict__ lamR0) {
-    const int64_t N = A.g.N;
-    const uint32_t y = xo[1] + yo[1];
-    const uint32_t m = tg > 0 ? uint32_t(tg) & 0xFFu : 0u;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) pby[i] += rb[0];
-    const double pz = A.k18 * pby[0];  // eq. 18 carries the adjoint of p_0 (if applied)
-    sto(lam0, y * 8u, tg >= 0 ? pby[0] : 0.0);
 #pragma unroll
     for (int i = 1; i < 9; ++i) {
-        const int io = opp<0>(i);
-        double acc = 0.0;
-        if (tg >= 0) {
-            if ((m >> (i - 1)) & 1u) {
-                const int64_t sl = int64_t(tg >> 8) * Q2_LINKS + (i - 1);
-                const double c1 = fabs(double(la[sl])), Bb = pby[io] - pz;
-                acc = c1 * Bb + pz;
-                lamR0[sl] = A.kF * (1.0 - c1) * Bb;
-            } else {
-                const double rbx = rb[kEy[i] * rs + kEx[i]];
-                const int tx = tag_at(i);
-                acc = pxi[i] + rbx;
-                if (tx > 0 && ((tx >> (i - 1)) & 1)) {
-                    const double ax = double(la[int64_t(tx >> 8) * Q2_LINKS + (i - 1)]);
-                    const uint32_t xs = xo[kEx[i] + 1] + yo[kEy[i] + 1];
-                    if (ax > 0.0) acc += (1.0 - ax) * (ldo(pbar + io * N, xs * 8u) + rbx - A.k18 * (ldo(pbar, xs * 8u) + rbx));
-                }
-            }
-            if ((m >> (io - 1)) & 1u) {
-                const double ao = double(la[int64_t(tg >> 8) * Q2_LINKS + (io - 1)]);
-                if (ao < 0.0) acc += (1.0 + ao) * (pby[i] - pz);
-            }
-        }
-        sto(lam0 + i * N, y * 8u, acc);
+        const double c2 = a[i - 1] > RC(0) && a[i - 1] < RC(1) ? 1.0 - double(a[i - 1]) : 0.0;
+        pb[i] += c2 * (pb[opp<0>(i)] - A.k18 * pb[0]);
     }
+}
+
+// Transposed streaming, links and eq. 18 at a fluid node (tag tg): lambda(t) and lambda_R(t) from pbar of its
+// neighbours x + e_i in direction i (pxi; pxi[0] its own), without the density adjoint, which rb holds
+// around the node (row stride rs); tag_at(i): the tag of x + e_i.
+template <class RC, class TagAt>
+__device__ __forceinline__ void stream_T9(const AdjDev& A, const RC* __restrict__ la, const double* __restrict__ pbar, int tg,
+                                          uint32_t y, const double (&pxi)[9], const double* rb, int rs, TagAt tag_at,
+                                          double* __restrict__ lam0, double* __restrict__ lamR0) {
+    const int64_t N = A.g.N;
+    double acc[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) acc[i] = pxi[i] + rb[kEy[i] * rs + kEx[i]];
+    const __amdgpu_buffer_rsrc_t rla = make_res(la, uint64_t(A.nb) * Q2_LINKS * sizeof(RC));
+    if (A.k18 == 0.0) {
+        // without eq. 18 the density part of a neighbour's c2 Bbar_i is left (see collide_T9)
+        RC ax[9];
+#pragma unroll
+        for (int i = 1; i < 9; ++i) {
+            const int tx = tag_at(i);
+            const bool lk = tx > 0 && ((tx >> (i - 1)) & 1);
+            ax[i] = Buf<RC>::ld(rla, lk ? (uint32_t(tx >> 8) * Q2_LINKS + uint32_t(i - 1)) * uint32_t(sizeof(RC)) : OOB);
+        }
+#pragma unroll
+        for (int i = 1; i < 9; ++i)
+            acc[i] += ax[i] > RC(0) && ax[i] < RC(1) ? (1.0 - double(ax[i])) * rb[kEy[i] * rs + kEx[i]] : 0.0;
+    }
+    if (tg > 0) {
+        RC a[Q2_LINKS];
+        double pby[9], lr[Q2_LINKS];
+        coefs(A, la, tg, a);
+#pragma unroll
+        for (int i = 1; i < 9; ++i) pby[i] = ldo(pbar + i * N, y * 8u) + rb[0];
+        const double pz = A.k18 * acc[0];  // eq. 18 carries the adjoint of p_0 (if applied)
+#pragma unroll
+        for (int i = 1; i < 9; ++i) {
+            const bool lk = (tg >> (i - 1)) & 1;
+            const double c1 = fabs(double(a[i - 1])), Bb = pby[opp<0>(i)] - pz;
+            acc[i] = lk ? c1 * Bb + pz : acc[i];
+            lr[i - 1] = lk ? A.kF * (1.0 - c1) * Bb : 0.0;
+        }
+        // eq. 17 of the link (x, opp i): o = f_i(x)
+#pragma unroll
+        for (int i = 1; i < 9; ++i) {
+            const double ao = double(a[opp<0>(i) - 1]);
+            acc[i] += ao < 0.0 ? (1.0 + ao) * (pby[i] - pz) : 0.0;
+        }
+        st_vec(make_res(lamR0, uint64_t(A.nb) * Q2_LINKS * 8u), uint32_t(tg >> 8) * (Q2_LINKS * 8u), lr);
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) sto(lam0 + i * N, y * 8u, acc[i]);
 }
 
 // the columns and rows around a node: index e + 1
@@ -294,9 +322,9 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_collide(AdjDev A, int nsx, const
     const int tg = ldo(A.tag, x * 4u);
     double v[9], lv[9];
     if (PULL) {
-        pops<S, true>(A, gt, cx, cy, v);
+        pops<S>(A, gt, cx, cy, v);
     } else {
-        const double r = rho0[x];
+        const double r = rho0[x] - A.rho_ref;
 #pragma unroll
         for (int i = 0; i < 9; ++i) v[i] = wgt<double>(0, i) * r;
     }
@@ -310,13 +338,11 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_collide(AdjDev A, int nsx, const
     const double rr = PULL ? density<S, RC>(A, gt, la, rec, tr, gx, gy) : rho0[xr];
     s_rho[ry * RX + rx] = rr;
     s_tag[ry * RX + rx] = tr;
-    if (PULL && tg > 0) links_on<S, RC, true>(A, gt, la, rec, tg, cx, cy, v);
+    if (PULL && tg > 0) links_on<RC>(A, la, rec, tg, v);
     // (here, so that they arrive during phase 2 without holding registers through the links)
 #pragma unroll
     for (int i = 0; i < 9; ++i) lv[i] = ldo(lam1 + i * N, x * 8u);
-    double r = 0.0;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) r += v[i];
+    const double r = sum9(A, v);
     s_rho[(ly + 2) * RX + lx + 2] = r;
     s_tag[(ly + 2) * RX + lx + 2] = tg;
     __syncthreads();
@@ -362,7 +388,7 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_collide(AdjDev A, int nsx, const
     const double gp = -A.G * P[0];
     const double F[2] = {gp * S2[0] + r * A.grav[0], gp * S2[1] + r * A.grav[1]};
     double pb[9], Fb[2];
-    collide_T9(A, r, jm, F, lv, tg, lamR1, pb, Fb);
+    collide_T9(A, la, r, jm, F, lv, tg, lamR1, pb, Fb);
 #pragma unroll
     for (int i = 0; i < 9; ++i) sto(pbar + i * N, x * 8u, pb[i]);
     sto(Fbar, x * 8u, Fb[0]);
@@ -391,7 +417,7 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_stream(AdjDev A, int nsx, const 
     // ---- 1 (every load that depends on no other is issued here)
     constexpr int NRL = (NR + NT - 1) / NT, NQL = (NQ + NT - 1) / NT;
     int gr[NRL];
-    double fx[NRL], fy[NRL], ps[NRL], dp[NQL], pby[9], pxi[9];
+    double fx[NRL], fy[NRL], ps[NRL], dp[NQL], pxi[9];
 #pragma unroll
     for (int h = 0; h < NRL; ++h) {
         const int e = min(t + h * NT, NR - 1);
@@ -414,10 +440,7 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_stream(AdjDev A, int nsx, const 
     around(cx, cy, nx, ny, xo, yo);
     if (STREAM) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            pby[i] = ldo(pbar + i * N, (xo[1] + yo[1]) * 8u);
-            if (i > 0) pxi[i] = ldo(pbar + i * N, (xo[kEx[i] + 1] + yo[kEy[i] + 1]) * 8u);
-        }
+        for (int i = 0; i < 9; ++i) pxi[i] = ldo(pbar + i * N, (xo[kEx[i] + 1] + yo[kEy[i] + 1]) * 8u);
     }
 #pragma unroll
     for (int h = 0; h < NRL; ++h) {
@@ -476,7 +499,8 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_stream(AdjDev A, int nsx, const 
     if (!own) return;
     const int c3 = (ly + 3) * RX + lx + 3, c2 = (ly + 2) * QX + lx + 2;
     const int tg = s_tag[c3];
-    stream_T9(A, la, pbar, tg, xo, yo, pby, pxi, s_rb + c2, QX, [&](int i) { return s_tag[c3 + kEy[i] * RX + kEx[i]]; }, lam0,
+    if (tg < 0) return;  // lambda is read on fluid nodes only
+    stream_T9(A, la, pbar, tg, xo[1] + yo[1], pxi, s_rb + c2, QX, [&](int i) { return s_tag[c3 + kEy[i] * RX + kEx[i]]; }, lam0,
               lamR0);
 }
 
@@ -561,18 +585,17 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_collide(AdjDev A, int nsx, co
     const bool own = T.x0 + lx < nx && T.y0 + ly < ny;
     const int tg = ldo(A.tag, x * 4u), c0 = (ly + HC) * RX + lx + HC;
     const int8_t lay = ldo(A.layer, x);
-    double v[9], lv[9], r = 0.0;
+    double v[9], lv[9];
     if (PULL) {
-        pops<S, true>(A, gt, cx, cy, v);
-        if (tg > 0) links_on<S, RC, true>(A, gt, la, rec, tg, cx, cy, v);
+        pops<S>(A, gt, cx, cy, v);
+        if (tg > 0) links_on<RC>(A, la, rec, tg, v);
     } else {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) v[i] = wgt<double>(0, i) * rho0[x];
+        for (int i = 0; i < 9; ++i) v[i] = wgt<double>(0, i) * (rho0[x] - A.rho_ref);
     }
 #pragma unroll
     for (int i = 0; i < 9; ++i) lv[i] = ldo(lam1 + i * N, x * 8u);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) r += v[i];
+    const double r = sum9(A, v);
     s_rho[c0] = lay == 0 ? r : 0.0;
     s_tag[c0] = tg;
     s_lay[c0] = lay;
@@ -626,7 +649,7 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_collide(AdjDev A, int nsx, co
     const double F[2] = {-r * diff1(U, 1) + diff1(R, 1) * (1.0 / 3.0) + r * A.grav[0],
                          -r * diff1(U, MX) + diff1(R, RX) * (1.0 / 3.0) + r * A.grav[1]};
     double pb[9], Fb[2];
-    collide_T9(A, r, jm, F, lv, tg, lamR1, pb, Fb);
+    collide_T9(A, la, r, jm, F, lv, tg, lamR1, pb, Fb);
 #pragma unroll
     for (int i = 0; i < 9; ++i) sto(pbar + i * N, x * 8u, pb[i]);
     sto(Fbar, x * 8u, Fb[0]);
@@ -669,13 +692,10 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, con
     const int c0 = (ly + H) * RX + lx + H;
     uint32_t xo[3], yo[3];
     around(image(T.x0 + lx, nx), image(T.y0 + ly, ny), nx, ny, xo, yo);
-    double pby[9], pxi[9];
+    double pxi[9];
     if (STREAM) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            pby[i] = ldo(pbar + i * N, (xo[1] + yo[1]) * 8u);
-            if (i > 0) pxi[i] = ldo(pbar + i * N, (xo[kEx[i] + 1] + yo[kEy[i] + 1]) * 8u);
-        }
+        for (int i = 0; i < 9; ++i) pxi[i] = ldo(pbar + i * N, (xo[kEx[i] + 1] + yo[kEy[i] + 1]) * 8u);
     }
     __syncthreads();
     // entries at most m nodes from the tile
@@ -765,8 +785,8 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, con
     }
     __syncthreads();
     // ---- 6
-    if (!own) return;
-    stream_T9(A, la, pbar, s_tag[c0], xo, yo, pby, pxi, s_rb + c0, RX, [&](int i) { return s_tag[c0 + kEy[i] * RX + kEx[i]]; },
+    if (!own || s_tag[c0] < 0) return;  // lambda is read on fluid nodes only
+    stream_T9(A, la, pbar, s_tag[c0], xo[1] + yo[1], pxi, s_rb + c0, RX, [&](int i) { return s_tag[c0 + kEy[i] * RX + kEx[i]]; },
               lam0, lamR0);
 }
 

@@ -34,7 +34,6 @@ struct Adj3 {
     AdjDev A;
     const int32_t* wl_node;
     int64_t n_wall;
-    uint32_t n_bnodes;
     AdjWork w;
 };
 
@@ -100,9 +99,9 @@ __global__ __launch_bounds__(NT) void k_adj3_pre(Adj3 p, const S* __restrict__ g
             // node's own populations
             RC h[RF3 + 18];
             double a[18];
-            ld_vec(make_res(rec, uint64_t(p.n_bnodes) * REC3 * sizeof(RC)),
+            ld_vec(make_res(rec, uint64_t(p.A.nb) * REC3 * sizeof(RC)),
                    tg > 0 ? uint32_t(tg - 1) * uint32_t(REC3 * sizeof(RC)) : OOB, h);
-            coefs(la, p.n_bnodes, tg, a);
+            coefs(la, p.A.nb, tg, a);
             const double kr = A.kF * double(h[0]), dx = double(h[1]), dy = double(h[2]), dz = double(h[3]);
             const double sx = double(h[4]), sy = double(h[5]), sz = double(h[6]), duu = double(h[7]);
             double dm = 0.0;
@@ -303,7 +302,7 @@ __global__ __launch_bounds__(NT) void k_adj3_rho_T(Adj3 p, const RC* __restrict_
 #pragma unroll
         for (int i = 1; i < 19; ++i) r += ((mk >> (i - 1)) & 1u) ? wgt<double>(1, i) * qb[i] : 0.0;
         __builtin_amdgcn_sched_barrier(0);  // (106 and 125 registers instead of 135 and 158)
-        coefs(la, p.n_bnodes, tg, a);
+        coefs(la, p.A.nb, tg, a);
 #pragma unroll
         for (int i = 0; i < 19; ++i) pb[i] = ldo(p.w.pbar + i * N, x);
         const double z = A.k18 * (pb[0] + r);
@@ -334,7 +333,7 @@ __global__ __launch_bounds__(NT) void k_adj3_stream(Adj3 p, const RC* __restrict
     for (int i = 0; i < 19; ++i) acc[i] += rb[i];
     if (tg > 0) {
         double a[18], pb[19];
-        coefs(la, p.n_bnodes, tg, a);
+        coefs(la, p.A.nb, tg, a);
         pb[0] = acc[0];
 #pragma unroll
         for (int i = 1; i < 19; ++i) pb[i] = ldo(p.w.pbar + i * N, x) + rb[0];
@@ -366,7 +365,6 @@ hipError_t adj3_t(mcb_ctx* c, const AdjWork& w, const void* gt, const void* rec,
     p.A = make_dev(c);
     p.wl_node = reinterpret_cast<const int32_t*>(c->lk + c->L.wl_node);
     p.n_wall = c->n_wall > 0 ? c->n_wall : 0;
-    p.n_bnodes = uint32_t(c->n_bnodes > 0 ? c->n_bnodes : 0);
     p.w = w;
     const RC* la = reinterpret_cast<const RC*>(c->lk + c->L.lk_a);
     const dim3 G(unsigned((c->g.N + NT - 1) / NT)), W(unsigned((p.n_wall + NT - 1) / NT)), B(NT);

@@ -36,7 +36,7 @@ struct AdjDev {
     const int32_t* tag;          // node tags (see the step kernels)
     const uint32_t* nmask;       // 3-D link bits
     const double* phi;           // wettability factor per wall node
-    int fs;                      // stride of the boundary records
+    uint32_t nb;                 // boundary nodes
     double tau, G, two_over_G, RT, a, b4, rho_ref;
     double kF, k18;              // boundary scheme: weights of the forcing term and of eq. 18
     double grav[3];              // body acceleration
@@ -102,7 +102,7 @@ AdjDev make_dev(const mcb_ctx* c) {
     A.tag = reinterpret_cast<const int32_t*>(c->lat + c->L.tag);
     A.nmask = reinterpret_cast<const uint32_t*>(c->lat + c->L.nmask);
     A.phi = reinterpret_cast<const double*>(c->lk + c->L.wl_phi);
-    A.fs = int(c->L.rec_stride);
+    A.nb = uint32_t(c->n_bnodes > 0 ? c->n_bnodes : 0);
     A.tau = c->p.tau;
     A.G = c->p.G;
     A.two_over_G = 2.0 / c->p.G;
