@@ -226,7 +226,7 @@ __device__ __forceinline__ void collide_T9(const AdjDev& A, const RC* __restrict
     for (int i = 0; i < 9; ++i) pb[i] = lt[i] + rb + (i == 0 ? 0.0 : edot(i, jb[0], jb[1]));
 #pragma unroll
     for (int i = 1; i < 9; ++i) {
-        const double c2 = a[i - 1] > RC(0) && a[i - 1] < RC(1) ? 1.0 - double(a[i - 1]) : 0.0;
+        const double c2 = a[i - 1] >= RC(0) && a[i - 1] < RC(1) ? 1.0 - double(a[i - 1]) : 0.0;
         pb[i] += c2 * (pb[opp<0>(i)] - A.k18 * pb[0]);
     }
 }
@@ -246,15 +246,16 @@ __device__ __forceinline__ void stream_T9(const AdjDev& A, const RC* __restrict_
     if (A.k18 == 0.0) {
         // without eq. 18 the density part of a neighbour's c2 Bbar_i is left (see collide_T9)
         RC ax[9];
+        bool lk[9];
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
             const int tx = tag_at(i);
-            const bool lk = tx > 0 && ((tx >> (i - 1)) & 1);
-            ax[i] = Buf<RC>::ld(rla, lk ? (uint32_t(tx >> 8) * Q2_LINKS + uint32_t(i - 1)) * uint32_t(sizeof(RC)) : OOB);
+            lk[i] = tx > 0 && ((tx >> (i - 1)) & 1);
+            ax[i] = Buf<RC>::ld(rla, lk[i] ? (uint32_t(tx >> 8) * Q2_LINKS + uint32_t(i - 1)) * uint32_t(sizeof(RC)) : OOB);
         }
 #pragma unroll
         for (int i = 1; i < 9; ++i)
-            acc[i] += ax[i] > RC(0) && ax[i] < RC(1) ? (1.0 - double(ax[i])) * rb[kEy[i] * rs + kEx[i]] : 0.0;
+            acc[i] += lk[i] && ax[i] >= RC(0) && ax[i] < RC(1) ? (1.0 - double(ax[i])) * rb[kEy[i] * rs + kEx[i]] : 0.0;
     }
     if (tg > 0) {
         RC a[Q2_LINKS];

@@ -308,7 +308,7 @@ __global__ __launch_bounds__(NT) void k_adj3_rho_T(Adj3 p, const RC* __restrict_
         const double z = A.k18 * (pb[0] + r);
 #pragma unroll
         for (int i = 1; i < 19; ++i)
-            if (a[i - 1] > 0.0 && a[i - 1] < 1.0) sto(p.w.pbar + i * N, x, pb[i] + (1.0 - a[i - 1]) * (pb[opp<1>(i)] + r - z));
+            if (a[i - 1] >= 0.0 && a[i - 1] < 1.0) sto(p.w.pbar + i * N, x, pb[i] + (1.0 - a[i - 1]) * (pb[opp<1>(i)] + r - z));
     }
     sto(p.w.rbar, x, r);
 }
