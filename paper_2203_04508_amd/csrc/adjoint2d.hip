@@ -6,7 +6,7 @@
 // launch is bound by one round trip per dependent load.  Here the intermediates of a tile stay in LDS
 // and registers, and only pbar, Fbar and the fields they belong to go from the first kernel to the
 // second.  A reverse step at 512^2 FP32 storage: 65 -> 25 us (14.3 the first kernel, 4.2 TB/s of what it
-// reads and writes, 10.6 the second); at 301 x 203 FP64 in the chemical-potential model 77 -> 23 us.
+// reads and writes, 10.6 the second); at 301 x 203 FP64 in the chemical-potential model 77 -> 20 us.
 // Tiles of 32 x 16 instead of 32 x 8 for the pseudopotential kernels measured the same (15.6 and 14.3
 // us); lambda loaded before the links instead of after spills 96 bytes a lane (22.7 us).
 //
@@ -18,8 +18,6 @@
 
 namespace mcb {
 namespace {
-
-constexpr int TX = 32, NT = 256, TY = NT / TX;
 
 __device__ constexpr int kEx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 __device__ constexpr int kEy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
@@ -46,7 +44,7 @@ __device__ __forceinline__ int image(int v, int m) {
 struct Tile {
     int x0, y0;
 };
-template <int TY>
+template <int TX, int TY>
 __device__ __forceinline__ Tile tile_of(int nsx) {
     const int nb = gridDim.x, bid = blockIdx.x, per = nb >> 3, rem = nb & 7, xcd = bid & 7, k8 = bid >> 3;
     const int l = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + k8;
@@ -54,7 +52,7 @@ __device__ __forceinline__ Tile tile_of(int nsx) {
 }
 
 // entry j of the ring of H nodes around a TX x TY tile, in the coordinates of the region of tile and ring
-template <int TY, int H>
+template <int TX, int TY, int H>
 __device__ __forceinline__ void ring_at(int j, int& rx, int& ry) {
     constexpr int RX = TX + 2 * H;
     const int q = j - 2 * H * RX;
@@ -298,17 +296,18 @@ __device__ __forceinline__ void around(int cx, int cy, int nx, int ny, uint32_t 
 // nodes wide, to LDS.  Phase 2: psi and its derivative on the tile and the nodes around it (wall nodes
 // by eq. 15).  Phase 3: lambda(t + 1) -> pbar (without the density terms) and Fbar of the own nodes.
 // PULL = false: the first collision, p = f^eq(rho0, 0).
-template <class S, class RC, bool PULL>
+// OWN lanes own the tile's nodes; lanes past them, where there are any, take the ring.
+template <class S, class RC, int TX, int OWN, int NT, bool PULL>
 __global__ __launch_bounds__(NT, 4) void k_adj2_collide(AdjDev A, int nsx, const S* __restrict__ gt, const RC* __restrict__ la,
                                                         const RC* __restrict__ rec, const double* __restrict__ rho0,
                                                         const double* __restrict__ lam1, const double* __restrict__ lamR1,
                                                         double* __restrict__ pbar, double* __restrict__ Fbar,
                                                         double* __restrict__ psi, double* __restrict__ dpsi,
                                                         double* __restrict__ rave, double* __restrict__ den) {
-    constexpr int RX = TX + 4, RY = TY + 4, NRING = RX * RY - TX * TY, PX = TX + 2, PY = TY + 2, NP = PX * PY;
+    constexpr int TY = OWN / TX, RX = TX + 4, RY = TY + 4, NRING = RX * RY - TX * TY, PX = TX + 2, PY = TY + 2, NP = PX * PY;
     __shared__ double s_rho[RY * RX], s_psi[NP];
     __shared__ int s_tag[RY * RX];
-    const Tile T = tile_of<TY>(nsx);
+    const Tile T = tile_of<TX, TY>(nsx);
     const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = A.g.nx, ny = A.g.ny;
     const int64_t N = A.g.N;
     auto node = [&](int rx, int ry, int& cx, int& cy) {
@@ -317,35 +316,45 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_collide(AdjDev A, int nsx, const
         return uint32_t(cy) * uint32_t(nx) + uint32_t(cx);
     };
     // ---- 1
+    constexpr bool SPLIT = OWN < NT;
+    static_assert(OWN % 64 == 0 && NRING <= (SPLIT ? NT - OWN : NT), "one ring node per lane");
+    const bool mine = !SPLIT || t < OWN;  // uniform in a wave
+    bool own = false;
+    uint32_t x = 0;
+    int tg = -1;
+    double v[9], lv[9], r = 0.0;
     int cx, cy;
-    const uint32_t x = node(lx + 2, ly + 2, cx, cy);
-    const bool own = T.x0 + lx < nx && T.y0 + ly < ny;
-    const int tg = ldo(A.tag, x * 4u);
-    double v[9], lv[9];
-    if (PULL) {
-        pops<S>(A, gt, cx, cy, v);
-    } else {
-        const double r = rho0[x] - A.rho_ref;
+    if (mine) {
+        x = node(lx + 2, ly + 2, cx, cy);
+        own = T.x0 + lx < nx && T.y0 + ly < ny;
+        tg = ldo(A.tag, x * 4u);
+        if (PULL) {
+            pops<S>(A, gt, cx, cy, v);
+        } else {
+            const double d = rho0[x] - A.rho_ref;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) v[i] = wgt<double>(0, i) * r;
+            for (int i = 0; i < 9; ++i) v[i] = wgt<double>(0, i) * d;
+        }
     }
-    // the ring; lanes past its last entry repeat it
-    int rx, ry;
-    ring_at<TY, 2>(min(t, NRING - 1), rx, ry);
-    static_assert(NRING <= NT, "one ring node per lane");
-    int gx, gy;
-    const uint32_t xr = node(rx, ry, gx, gy);
-    const int tr = ldo(A.tag, xr * 4u);
-    const double rr = PULL ? density<S, RC>(A, gt, la, rec, tr, gx, gy) : rho0[xr];
-    s_rho[ry * RX + rx] = rr;
-    s_tag[ry * RX + rx] = tr;
-    if (PULL && tg > 0) links_on<RC>(A, la, rec, tg, v);
-    // (here, so that they arrive during phase 2 without holding registers through the links)
+    if (!SPLIT || !mine) {
+        // the ring; lanes past its last entry repeat it
+        int rx, ry, gx, gy;
+        ring_at<TX, TY, 2>(min(SPLIT ? t - OWN : t, NRING - 1), rx, ry);
+        const uint32_t xr = node(rx, ry, gx, gy);
+        const int tr = ldo(A.tag, xr * 4u);
+        const double rr = PULL ? density<S, RC>(A, gt, la, rec, tr, gx, gy) : rho0[xr];
+        s_rho[ry * RX + rx] = rr;
+        s_tag[ry * RX + rx] = tr;
+    }
+    if (mine) {
+        if (PULL && tg > 0) links_on<RC>(A, la, rec, tg, v);
+        // (here, so that they arrive during phase 2 without holding registers through the links)
 #pragma unroll
-    for (int i = 0; i < 9; ++i) lv[i] = ldo(lam1 + i * N, x * 8u);
-    const double r = sum9(A, v);
-    s_rho[(ly + 2) * RX + lx + 2] = r;
-    s_tag[(ly + 2) * RX + lx + 2] = tg;
+        for (int i = 0; i < 9; ++i) lv[i] = ldo(lam1 + i * N, x * 8u);
+        r = sum9(A, v);
+        s_rho[(ly + 2) * RX + lx + 2] = r;
+        s_tag[(ly + 2) * RX + lx + 2] = tg;
+    }
     __syncthreads();
     // ---- 2
 #pragma unroll
@@ -401,18 +410,18 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_collide(AdjDev A, int nsx, const
 // Phase 2: psibar -> rhobar of the fluid nodes next to or in the tile, and of the wall nodes up to two
 // nodes out their density adjoint per unit eq. 15 weight (and dphi of the own ones).  Phase 3: the
 // density adjoint of the tile and the nodes around it.  Phase 4 (STREAM): lambda(t) and lambda_R(t).
-template <class RC, bool STREAM>
+template <class RC, int TX, int OWN, int NT, bool STREAM>
 __global__ __launch_bounds__(NT, 4) void k_adj2_stream(AdjDev A, int nsx, const RC* __restrict__ la,
                                                        const double* __restrict__ psi, const double* __restrict__ dpsi,
                                                        const double* __restrict__ rave, const double* __restrict__ den,
                                                        const double* __restrict__ Fbar, const double* __restrict__ pbar,
                                                        double* __restrict__ dphi, double* __restrict__ lam0,
                                                        double* __restrict__ lamR0) {
-    constexpr int RX = TX + 6, RY = TY + 6, NR = RX * RY, QX = TX + 4, QY = TY + 4, NQ = QX * QY;
+    constexpr int TY = OWN / TX, RX = TX + 6, RY = TY + 6, NR = RX * RY, QX = TX + 4, QY = TY + 4, NQ = QX * QY;
     constexpr int PX = TX + 2, PY = TY + 2, NP = PX * PY;
     __shared__ double s_psi[NR], s_fx[NR], s_fy[NR], s_q[NQ], s_rb[NQ];
     __shared__ int s_tag[NR];
-    const Tile T = tile_of<TY>(nsx);
+    const Tile T = tile_of<TX, TY>(nsx);
     const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = A.g.nx, ny = A.g.ny;
     const int64_t N = A.g.N;
     // ---- 1 (every load that depends on no other is issued here)
@@ -435,11 +444,11 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_stream(AdjDev A, int nsx, const 
         yq[h] = uint32_t(image(T.y0 - 2 + e / QX, ny)) * uint32_t(nx) + uint32_t(image(T.x0 - 2 + e % QX, nx));
         dp[h] = ldo(dpsi, yq[h] * 8u);
     }
-    const bool own = T.x0 + lx < nx && T.y0 + ly < ny;
+    const bool own = (OWN == NT || t < OWN) && T.x0 + lx < nx && T.y0 + ly < ny;
     const int cx = image(T.x0 + lx, nx), cy = image(T.y0 + ly, ny);
     uint32_t xo[3], yo[3];
     around(cx, cy, nx, ny, xo, yo);
-    if (STREAM) {
+    if (STREAM && (OWN == NT || t < OWN)) {
 #pragma unroll
         for (int i = 0; i < 9; ++i) pxi[i] = ldo(pbar + i * N, (xo[kEx[i] + 1] + yo[kEy[i] + 1]) * 8u);
     }
@@ -506,12 +515,9 @@ __global__ __launch_bounds__(NT, 4) void k_adj2_stream(AdjDev A, int nsx, const 
 }
 
 // ================================================================ chemical-potential model
-// The same two kernels with that model's fields between the density and the force (32 x 16 tiles, 512
-// lanes): the solid layers' densities (eq. 15), mu (eq. 12) and F (eq. 9) of the recomputed state, and
+// The same two kernels with that model's fields between the density and the force: the solid layers' densities (eq. 15), mu (eq. 12) and F (eq. 9) of the recomputed state, and
 // their transposes.  Fourth-order central differences: d/dx v = sum_m c_m v(x + m), m = -2..2,
 // c = (1, -8, 0, 8, -1) / 12; d2/dx2 v = sum_m d_m v(x + m), d = (-1, 16, -30, 16, -1) / 12.
-constexpr int CNT = 512, CTY = CNT / TX;
-
 __device__ constexpr double cdc(int m) { return m == -2 ? 1.0 / 12.0 : m == -1 ? -8.0 / 12.0 : m == 1 ? 8.0 / 12.0 : m == 2 ? -1.0 / 12.0 : 0.0; }
 __device__ constexpr double cdd(int m) { return (m == -2 || m == 2) ? -1.0 / 12.0 : (m == -1 || m == 1) ? 16.0 / 12.0 : -30.0 / 12.0; }
 
@@ -548,18 +554,18 @@ __device__ __forceinline__ void around_layer(const int8_t* lay, int c, int st, i
 
 // ---- first kernel: as k_adj2_collide, with the fields of a ring of six nodes (as the forward tiles).
 // rho and mu of every node go to the second kernel.
-template <class S, class RC, bool PULL>
-__global__ __launch_bounds__(CNT, 4) void k_adj2cp_collide(AdjDev A, int nsx, const S* __restrict__ gt, const RC* __restrict__ la,
+template <class S, class RC, int TX, int OWN, int NT, bool PULL>
+__global__ __launch_bounds__(NT, 4) void k_adj2cp_collide(AdjDev A, int nsx, const S* __restrict__ gt, const RC* __restrict__ la,
                                                            const RC* __restrict__ rec, const double* __restrict__ rho0,
                                                            const double* __restrict__ lam1, const double* __restrict__ lamR1,
                                                            double* __restrict__ pbar, double* __restrict__ Fbar,
                                                            double* __restrict__ rho, double* __restrict__ mu) {
-    constexpr int HC = 6, RX = TX + 2 * HC, RY = CTY + 2 * HC, NR = RX * RY, NRING = NR - TX * CTY;
-    constexpr int MX = TX + 4, MY = CTY + 4, NM = MX * MY;
+    constexpr int TY = OWN / TX, HC = 6, RX = TX + 2 * HC, RY = TY + 2 * HC, NR = RX * RY, NRING = NR - TX * TY;
+    constexpr int MX = TX + 4, MY = TY + 4, NM = MX * MY;
     __shared__ double s_rho[NR], s_mu[NM];
     __shared__ int s_tag[NR];
     __shared__ int8_t s_lay[NR];
-    const Tile T = tile_of<CTY>(nsx);
+    const Tile T = tile_of<TX, TY>(nsx);
     const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = A.g.nx, ny = A.g.ny;
     const int64_t N = A.g.N;
     auto node = [&](int rx, int ry, int& cx, int& cy) {
@@ -569,9 +575,10 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_collide(AdjDev A, int nsx, co
     };
     // ---- 1: densities, layers and tags
     bool solid = false;
-    for (int k = t; k < NRING; k += CNT) {
+    const bool mine = OWN == NT || t < OWN;  // uniform in a wave
+    for (int k = OWN == NT ? t : (t >= OWN ? t - OWN : t + NT - OWN); k < NRING; k += NT) {
         int rx, ry, gx, gy;
-        ring_at<CTY, HC>(k, rx, ry);
+        ring_at<TX, TY, HC>(k, rx, ry);
         const uint32_t x = node(rx, ry, gx, gy);
         const int g = ldo(A.tag, x * 4u);
         const int8_t l = ldo(A.layer, x);
@@ -581,31 +588,37 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_collide(AdjDev A, int nsx, co
         s_lay[ry * RX + rx] = l;
         solid = solid || l == 1 || l == 2;
     }
-    int cx, cy;
-    const uint32_t x = node(lx + HC, ly + HC, cx, cy);
-    const bool own = T.x0 + lx < nx && T.y0 + ly < ny;
-    const int tg = ldo(A.tag, x * 4u), c0 = (ly + HC) * RX + lx + HC;
-    const int8_t lay = ldo(A.layer, x);
-    double v[9], lv[9];
-    if (PULL) {
-        pops<S>(A, gt, cx, cy, v);
-        if (tg > 0) links_on<RC>(A, la, rec, tg, v);
-    } else {
+    uint32_t x = 0;
+    bool own = false;
+    int tg = -1;
+    const int c0 = (ly + HC) * RX + lx + HC;
+    double v[9], lv[9], r = 0.0;
+    if (mine) {
+        int cx, cy;
+        x = node(lx + HC, ly + HC, cx, cy);
+        own = T.x0 + lx < nx && T.y0 + ly < ny;
+        tg = ldo(A.tag, x * 4u);
+        const int8_t lay = ldo(A.layer, x);
+        if (PULL) {
+            pops<S>(A, gt, cx, cy, v);
+            if (tg > 0) links_on<RC>(A, la, rec, tg, v);
+        } else {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) v[i] = wgt<double>(0, i) * (rho0[x] - A.rho_ref);
+            for (int i = 0; i < 9; ++i) v[i] = wgt<double>(0, i) * (rho0[x] - A.rho_ref);
+        }
+#pragma unroll
+        for (int i = 0; i < 9; ++i) lv[i] = ldo(lam1 + i * N, x * 8u);
+        r = sum9(A, v);
+        s_rho[c0] = lay == 0 ? r : 0.0;
+        s_tag[c0] = tg;
+        s_lay[c0] = lay;
+        solid = solid || lay == 1 || lay == 2;
     }
-#pragma unroll
-    for (int i = 0; i < 9; ++i) lv[i] = ldo(lam1 + i * N, x * 8u);
-    const double r = sum9(A, v);
-    s_rho[c0] = lay == 0 ? r : 0.0;
-    s_tag[c0] = tg;
-    s_lay[c0] = lay;
-    solid = solid || lay == 1 || lay == 2;
     // ---- 2, 3: the solid layers
     if (__syncthreads_or(solid)) {
 #pragma unroll 1
         for (int l = 1; l <= 2; ++l) {
-            for (int e = t; e < NR; e += CNT) {
+            for (int e = t; e < NR; e += NT) {
                 const int ex = e % RX, ey = e / RX;
                 if (ex >= l && ex < RX - l && ey >= l && ey < RY - l && s_lay[e] == l) {
                     double num, den;
@@ -617,7 +630,7 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_collide(AdjDev A, int nsx, co
         }
     }
     // ---- 4: mu
-    for (int j = t; j < NM; j += CNT) {
+    for (int j = t; j < NM; j += NT) {
         const int e = (j / MX + HC - 2) * RX + j % MX + HC - 2;
         const int l = s_lay[e];
         double m = 0.0;
@@ -664,21 +677,21 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_collide(AdjDev A, int nsx, co
 // transposed Laplacian).  Phase 4: the second layer's rhobar onto the first, and that per unit eq. 15
 // weight of its fluid neighbours, two nodes around.  Phase 5: the density adjoint of the fluid nodes
 // next to or in the tile.  Phase 6: transposed streaming.
-template <class RC, bool STREAM>
-__global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, const RC* __restrict__ la,
+template <class RC, int TX, int OWN, int NT, bool STREAM>
+__global__ __launch_bounds__(NT, 4) void k_adj2cp_stream(AdjDev A, int nsx, const RC* __restrict__ la,
                                                           const double* __restrict__ rho, const double* __restrict__ mu,
                                                           const double* __restrict__ Fbar, const double* __restrict__ pbar,
                                                           double* __restrict__ dphi, double* __restrict__ lam0,
                                                           double* __restrict__ lamR0) {
-    constexpr int H = 7, RX = TX + 2 * H, RY = CTY + 2 * H, NR = RX * RY;
+    constexpr int TY = OWN / TX, H = 7, RX = TX + 2 * H, RY = TY + 2 * H, NR = RX * RY;
     __shared__ double s_f[2][NR], s_r[NR], s_u[NR], s_ub[NR], s_rb[NR];
     __shared__ int s_tag[NR];
     __shared__ int8_t s_lay[NR];
-    const Tile T = tile_of<CTY>(nsx);
+    const Tile T = tile_of<TX, TY>(nsx);
     const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = A.g.nx, ny = A.g.ny;
     const int64_t N = A.g.N;
     // ---- 1
-    for (int e = t; e < NR; e += CNT) {
+    for (int e = t; e < NR; e += NT) {
         const uint32_t x = uint32_t(image(T.y0 - H + e / RX, ny)) * uint32_t(nx) + uint32_t(image(T.x0 - H + e % RX, nx));
         const int8_t l = ldo(A.layer, x);
         const double fx = ldo(Fbar, x * 8u), fy = ldo(Fbar + N, x * 8u);
@@ -689,12 +702,13 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, con
         s_f[0][e] = l == 0 ? fx : 0.0;
         s_f[1][e] = l == 0 ? fy : 0.0;
     }
-    const bool own = T.x0 + lx < nx && T.y0 + ly < ny;
-    const int c0 = (ly + H) * RX + lx + H;
+    const bool mine = OWN == NT || t < OWN;  // uniform in a wave
+    const bool own = mine && T.x0 + lx < nx && T.y0 + ly < ny;
+    const int c0 = mine ? (ly + H) * RX + lx + H : 0;
     uint32_t xo[3], yo[3];
     around(image(T.x0 + lx, nx), image(T.y0 + ly, ny), nx, ny, xo, yo);
     double pxi[9];
-    if (STREAM) {
+    if (STREAM && mine) {
 #pragma unroll
         for (int i = 0; i < 9; ++i) pxi[i] = ldo(pbar + i * N, (xo[kEx[i] + 1] + yo[kEy[i] + 1]) * 8u);
     }
@@ -702,10 +716,10 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, con
     // entries at most m nodes from the tile
     auto within = [&](int e, int m) {
         const int ex = e % RX, ey = e / RX;
-        return ex >= H - m && ex < TX + H + m && ey >= H - m && ey < CTY + H + m;
+        return ex >= H - m && ex < TX + H + m && ey >= H - m && ey < TY + H + m;
     };
     // ---- 2 (a node x = y - d e_k off the fluid has Fbar = 0)
-    for (int e = t; e < NR; e += CNT) {
+    for (int e = t; e < NR; e += NT) {
         double ub = 0.0;
         if (within(e, 5) && s_lay[e] <= 2) {
 #pragma unroll
@@ -734,7 +748,7 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, con
         dphi[-s_tag[c0] - 2] += g;
     }
     if (!STREAM) return;
-    for (int e = t; e < NR; e += CNT) {
+    for (int e = t; e < NR; e += NT) {
         const int l = s_lay[e];
         double rb = 0.0;
         if (within(e, 3) && l <= 2) {
@@ -755,7 +769,7 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, con
     }
     __syncthreads();
     // ---- 4 (into s_ub, which nothing reads any more)
-    for (int e = t; e < NR; e += CNT) {
+    for (int e = t; e < NR; e += NT) {
         double q = 0.0;
         if (within(e, 2) && s_lay[e] == 1) {
             q = s_rb[e];
@@ -776,7 +790,7 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, con
     }
     __syncthreads();
     // ---- 5 (each entry is read by its own lane alone)
-    for (int e = t; e < NR; e += CNT) {
+    for (int e = t; e < NR; e += NT) {
         if (within(e, 1) && s_lay[e] == 0) {
             double rb = s_rb[e];
 #pragma unroll
@@ -791,38 +805,74 @@ __global__ __launch_bounds__(CNT, 4) void k_adj2cp_stream(AdjDev A, int nsx, con
               lam0, lamR0);
 }
 
-template <class S, class RC>
-hipError_t adj2_t(mcb_ctx* c, const AdjWork& w, const void* gt, const void* fv, int pull, const double* lam1,
-                  const double* lamR1, double* lam0, double* lamR0) {
+// the two kernels on tiles of TX x OWN / TX nodes, NT lanes a workgroup
+struct Adj2 {
+    mcb_ctx* c;
+    const AdjWork& w;
+    const void *gt, *rec;
+    int pull;
+    const double *lam1, *lamR1;
+    double *lam0, *lamR0;
+};
+template <class S, class RC, int TX, int OWN, int NT, bool CP>
+hipError_t launch2(const Adj2& p) {
+    constexpr int TY = OWN / TX;
+    mcb_ctx* c = p.c;
+    const AdjWork& w = p.w;
     const AdjDev A = make_dev(c);
     const int nsx = (c->p.nx + TX - 1) / TX;
     const RC* la = reinterpret_cast<const RC*>(c->lk + c->L.lk_a);
-    if (A.cp) {
-        const dim3 grid(unsigned(nsx) * unsigned((c->p.ny + CTY - 1) / CTY)), blk(CNT);
-        hipLaunchKernelGGL((pull ? k_adj2cp_collide<S, RC, true> : k_adj2cp_collide<S, RC, false>), grid, blk, 0, c->stream, A,
-                           nsx, static_cast<const S*>(gt), la, static_cast<const RC*>(fv), w.rho0, lam1, lamR1, w.pbar, w.Fbar,
-                           w.rho, w.psi);
-        hipLaunchKernelGGL((pull ? k_adj2cp_stream<RC, true> : k_adj2cp_stream<RC, false>), grid, blk, 0, c->stream, A, nsx, la,
-                           w.rho, w.psi, w.Fbar, w.pbar, w.dphi, lam0, lamR0);
-        return hipGetLastError();
-    }
     const dim3 grid(unsigned(nsx) * unsigned((c->p.ny + TY - 1) / TY)), blk(NT);
-    hipLaunchKernelGGL((pull ? k_adj2_collide<S, RC, true> : k_adj2_collide<S, RC, false>), grid, blk, 0, c->stream, A, nsx,
-                       static_cast<const S*>(gt), la, static_cast<const RC*>(fv), w.rho0, lam1, lamR1, w.pbar, w.Fbar, w.psi,
-                       w.dpsi, w.rave, w.den);
-    hipLaunchKernelGGL((pull ? k_adj2_stream<RC, true> : k_adj2_stream<RC, false>), grid, blk, 0, c->stream, A, nsx, la, w.psi,
-                       w.dpsi, w.rave, w.den, w.Fbar, w.pbar, w.dphi, lam0, lamR0);
+    if constexpr (CP) {
+        hipLaunchKernelGGL((p.pull ? k_adj2cp_collide<S, RC, TX, OWN, NT, true> : k_adj2cp_collide<S, RC, TX, OWN, NT, false>), grid,
+                           blk, 0, c->stream, A, nsx, static_cast<const S*>(p.gt), la, static_cast<const RC*>(p.rec), w.rho0,
+                           p.lam1, p.lamR1, w.pbar, w.Fbar, w.rho, w.psi);
+        hipLaunchKernelGGL((p.pull ? k_adj2cp_stream<RC, TX, OWN, NT, true> : k_adj2cp_stream<RC, TX, OWN, NT, false>), grid, blk, 0,
+                           c->stream, A, nsx, la, w.rho, w.psi, w.Fbar, w.pbar, w.dphi, p.lam0, p.lamR0);
+    } else {
+        hipLaunchKernelGGL((p.pull ? k_adj2_collide<S, RC, TX, OWN, NT, true> : k_adj2_collide<S, RC, TX, OWN, NT, false>), grid, blk,
+                           0, c->stream, A, nsx, static_cast<const S*>(p.gt), la, static_cast<const RC*>(p.rec), w.rho0, p.lam1,
+                           p.lamR1, w.pbar, w.Fbar, w.psi, w.dpsi, w.rave, w.den);
+        hipLaunchKernelGGL((p.pull ? k_adj2_stream<RC, TX, OWN, NT, true> : k_adj2_stream<RC, TX, OWN, NT, false>), grid, blk, 0,
+                           c->stream, A, nsx, la, w.psi, w.dpsi, w.rave, w.den, w.Fbar, w.pbar, w.dphi, p.lam0, p.lamR0);
+    }
     return hipGetLastError();
+}
+
+// The forward step's rules (tile2d.hip), for the same reason: a box whose tiles are all resident waits for the
+// chain of one of them, which more lanes shorten.  Pseudopotential model (128 registers: two tiles of seven
+// waves a compute unit): a gradient of 50 steps at 64 x 60 1.56 -> 1.28 ms, 200 x 190 1.62 -> 1.49,
+// 256 x 250 1.86 -> 1.70, 350 x 360 1.81 -> 1.77; 512^2, four tiles a unit, 2.94 -> 3.06.  Chemical
+// potential, against 32 x 16 tiles of 512 lanes: 64 x 60 2.80 -> 1.90 ms, 301 x 203 3.14 -> 2.58, 500 x 300
+// 3.23 -> 2.98, 512 x 384 3.58 -> 3.27.
+template <class S, class RC>
+hipError_t adj2_t(const Adj2& p) {
+    const mcb_ctx* c = p.c;
+    auto tiles = [&](int tx, int ty) { return int64_t((c->p.nx + tx - 1) / tx) * ((c->p.ny + ty - 1) / ty); };
+    auto fits = [&](int tx, int ty) { return tiles(tx, ty) <= c->n_cu; };
+    if (c->p.model == MCB_MODEL_CHEMPOT) {
+        if (fits(8, 8)) return launch2<S, RC, 8, 64, 448, true>(p);
+        if (fits(16, 8)) return launch2<S, RC, 16, 128, 576, true>(p);
+        if (fits(16, 16)) return launch2<S, RC, 16, 256, 768, true>(p);
+        if (fits(32, 16)) return launch2<S, RC, 32, 512, 1024, true>(p);
+        if (fits(32, 20)) return launch2<S, RC, 32, 640, 1024, true>(p);
+        if (fits(32, 24)) return launch2<S, RC, 32, 768, 1024, true>(p);
+        return launch2<S, RC, 32, 512, 512, true>(p);
+    }
+    if (tiles(8, 8) <= 3 * c->n_cu) return launch2<S, RC, 8, 64, 192, false>(p);
+    if (tiles(32, 8) <= 2 * c->n_cu) return launch2<S, RC, 32, 256, 448, false>(p);
+    return launch2<S, RC, 32, 256, 256, false>(p);
 }
 
 }  // namespace
 
 hipError_t adj_step2d(mcb_ctx* c, const AdjWork& w, const void* gt, const void* rec, int pull, const double* lam1,
                       const double* lamR1, double* lam0, double* lamR0) {
+    const Adj2 p{c, w, gt, rec, pull, lam1, lamR1, lam0, lamR0};
     switch (c->p.precision) {
-        case MCB_F64: return adj2_t<double, double>(c, w, gt, rec, pull, lam1, lamR1, lam0, lamR0);
-        case MCB_F32S: return adj2_t<float, float>(c, w, gt, rec, pull, lam1, lamR1, lam0, lamR0);
-        default: return adj2_t<__half, float>(c, w, gt, rec, pull, lam1, lamR1, lam0, lamR0);
+        case MCB_F64: return adj2_t<double, double>(p);
+        case MCB_F32S: return adj2_t<float, float>(p);
+        default: return adj2_t<__half, float>(p);
     }
 }
 

@@ -90,29 +90,31 @@ __device__ __forceinline__ void ring_at(int j, int& rx, int& ry) {
 }
 
 // ---------------------------------------------------------------- pseudopotential model
-// A workgroup of NT lanes owns a tile of TX x TY nodes, TY = RPL NT / TX; lane t owns column t % TX
-// of rows t / TX + r NT / TX.  Three phases, two barriers:
-//   1  every lane pulls its own nodes and up to NRL nodes of the ring two nodes wide around the tile
-//      (psi of the ring next to the tile needs, through the wall nodes, the density two nodes out),
-//      applies eqs. 16-18 to its own, and puts the densities of the (TX + 4) x (TY + 4) region in LDS: a wall
-//      node's entry is minus its eq. 15 factor, any other solid node's is zero;
+// A workgroup owns a tile of TX x TY nodes, TY = OWN / TX; lane t < OWN owns column t % TX of row t / TX.
+// Three phases, two barriers:
+//   1  every node of the tile and of the ring two nodes wide around it is pulled by one lane (psi of the
+//      ring next to the tile needs, through the wall nodes, the density two nodes out); eqs. 16-18 are
+//      applied to the tile's own, and the densities of the (TX + 4) x (TY + 4) region go to LDS: a wall
+//      node's entry is minus its eq. 15 factor, any other solid node's is zero.  Lanes past the own ones pull
+//      the ring (OWN < NT), or the own lanes pull a node of it too (OWN = NT);
 //   2  psi of the (TX + 2) x (TY + 2) region, wall nodes from the entries around them (eq. 15);
 //   3  force, collision, store and boundary record of the own nodes, whose populations stayed in
 //      registers.
 // Why tiles here: a march gives a workgroup one row at a time, a serial chain of about 2 us per row on
 // a box that leaves most of the chip idle; a tile runs its whole chain once (one round of loads,
 // then the loads that depend on the tags, and two barriers).  Time per step, one-wave row march against
-// tiles: 64^2 FP64 24.5 -> 5.3 us, 512^2 FP32 20.3 -> 8.6, 1024^2 FP32 32.6 -> 20.8 (3.6 TB/s of populations),
-// FP64 61.6 -> 35.6 (4.3 TB/s), 1531 x 1021 FP64 81 -> 49.  About 16 rounds of 550 vector instructions
+// tiles: 64^2 FP64 24.5 -> 4.4 us, 512^2 FP32 20.3 -> 8.0, 1024^2 FP32 32.6 -> 19.7 (3.8 TB/s of populations),
+// FP64 61.6 -> 31.9 (4.7 TB/s), 1531 x 1021 FP64 81 -> 45.  About 16 rounds of 550 vector instructions
 // per SIMD make up two thirds of the 1024^2 FP32 time.
 // Every node past the box's edge is its periodic image, so partial tiles need no cases of their own:
 // they only do not store.
 // WPE: waves per SIMD the registers are bounded to.
-template <class S, class C, int TX, int NT, int RPL, int WPE, bool PULL, bool MRT>
+template <class S, class C, int TX, int NT, int OWN, int WPE, bool PULL, bool MRT>
 __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
-    constexpr int LY = NT / TX, TY = LY * RPL;
-    constexpr int RX = TX + 4, RY = TY + 4, PX = TX + 2, PY = TY + 2;
-    constexpr int NRING = RX * RY - TX * TY, NRL = (NRING + NT - 1) / NT;
+    constexpr int TY = OWN / TX;
+    constexpr int RX = TX + 4, RY = TY + 4, PX = TX + 2, PY = TY + 2, NRING = RX * RY - TX * TY;
+    constexpr bool SPLIT = OWN < NT;  // the lanes past the own ones pull the ring
+    static_assert(OWN % 64 == 0 && NRING <= (SPLIT ? NT - OWN : NT), "one ring node per lane");
     constexpr int NP = PX * PY, NPL = (NP + NT - 1) / NT;
     constexpr uint32_t s = sizeof(S), sc = sizeof(C);
     __shared__ C s_rho[RY * RX];
@@ -124,6 +126,7 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
     const int logical = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + k8;
     const int x0 = (logical % a.nsx) * TX, y0 = (logical / a.nsx) * TY;
     const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = a.nx, ny = a.ny;
+    const bool mine = !SPLIT || t < OWN;  // uniform in a wave
     const uint32_t n = uint32_t(nx) * uint32_t(ny), ns = n * s;
     const __amdgpu_buffer_rsrc_t rfa = res32(a.fa, 9u * ns), rfb = res32(a.fb, 9u * ns);
     const __amdgpu_buffer_rsrc_t rtag = res32(a.tag, n * 4u), rfac = res32(a.fac, a.n_wall * sc);
@@ -135,33 +138,31 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
     bool bad = false;
 
     // ---- 1: tags first, then the populations (the loads that depend on a tag follow both)
-    int tg[RPL], tgr[NRL], pr[NRL];  // tags of the own and ring nodes, region entry of the ring nodes
-    C f[RPL][9], fr[NRL][9];
+    constexpr int K = SPLIT ? 1 : 2;  // nodes a lane pulls: its own (or its ring) node, its ring node
+    int tg[K], at[K];                 // their tags and region entries
+    C f[K][9];
     // INNER: the region and the nodes around it lie inside the box (all but the tiles along its edges)
     auto load = [&](auto in) {
         constexpr bool INNER = decltype(in)::value;
-        int cx[RPL + NRL], cy[RPL + NRL];
+        int cx[K], cy[K];
 #pragma unroll
-        for (int k = 0; k < RPL + NRL; ++k) {
-            int rx = lx + 2, ry = ly + k * LY + 2;
-            if (k >= RPL) {
-                // lanes past the ring's last entry repeat it
-                ring_at<TX, TY, 2>(min(t + (k - RPL) * NT, NRING - 1), rx, ry);
-                pr[k - RPL] = ry * RX + rx;
-            }
+        for (int k = 0; k < K; ++k) {
+            int rx = lx + 2, ry = ly + 2;
+            // lanes past the ring's last entry repeat it
+            if (k == 1 || !mine) ring_at<TX, TY, 2>(min(SPLIT ? t - OWN : t, NRING - 1), rx, ry);
+            at[k] = ry * RX + rx;
             cx[k] = INNER ? x0 - 2 + rx : image(x0 - 2 + rx, nx);
             cy[k] = INNER ? y0 - 2 + ry : image(y0 - 2 + ry, ny);
-            (k < RPL ? tg[k < RPL ? k : 0] : tgr[k < RPL ? 0 : k - RPL]) = ld_i32(rtag, (uint32_t(cy[k]) * uint32_t(nx) + uint32_t(cx[k])) * 4u);
+            tg[k] = ld_i32(rtag, (uint32_t(cy[k]) * uint32_t(nx) + uint32_t(cx[k])) * 4u);
         }
 #pragma unroll
-        for (int k = 0; k < RPL + NRL; ++k)
-            pull_at<S, C, PULL, INNER>(rfa, cx[k], cy[k], nx, ny, k < RPL ? f[k < RPL ? k : 0] : fr[k < RPL ? 0 : k - RPL]);
+        for (int k = 0; k < K; ++k) pull_at<S, C, PULL, INNER>(rfa, cx[k], cy[k], nx, ny, f[k]);
     };
     if (x0 >= 3 && y0 >= 3 && x0 + TX + 3 <= nx && y0 + TY + 3 <= ny)
         load(std::true_type{});
     else
         load(std::false_type{});
-    C ds[RPL], er[RPL];
+    C ds = C(0), er = C(0);
     auto sum9 = [](const C (&v)[9]) {
         C sr = C(0);
 #pragma unroll
@@ -179,32 +180,32 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
         d = apply_links<S, C>(g > 0, head, ca, v, a.kF, a.k18, e);
         return rec[RF2 + 8];
     };
-    auto put = [&](int at, int g, C sr) {
-        const C fac = Buf<C>::ld(rfac, g <= -2 ? uint32_t(-g - 2) * sc : OOB);
+    // what depends on the tags alone, before the links wait for their loads (1024^2 FP64 34.4 -> 31.9 us)
+    C fac[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) fac[k] = Buf<C>::ld(rfac, tg[k] <= -2 ? uint32_t(-tg[k] - 2) * sc : OOB);
+    constexpr int KR = K - 1;  // the ring node
+    C ls_ring = C(0);
+    if (link_sum && (!SPLIT || !mine))
+        ls_ring = Buf<C>::ld(rin, tg[KR] > 0 ? uint32_t(tg[KR] >> 8) * (REC2 * sc) + (RF2 + 8) * sc : OOB);
+    auto put = [&](int k, C sr) {
         const C rho = sr + a.rho_ref;
-        if (!(g >= 0 ? rho > C(0) : (g == -1 || fac > C(0)))) bad = true;  // the signs carry meaning below
-        s_rho[at] = g >= 0 ? rho : (g == -1 ? C(0) : -fac);
+        const int g = tg[k];
+        if (!(g >= 0 ? rho > C(0) : (g == -1 || fac[k] > C(0)))) bad = true;  // the signs carry meaning below
+        s_rho[at[k]] = g >= 0 ? rho : (g == -1 ? C(0) : -fac[k]);
     };
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        C sr = sum9(f[r]);
-        ds[r] = er[r] = C(0);
-        if (PULL && __any(tg[r] > 0)) {
-            const C ls = links(tg[r], f[r], ds[r], er[r]);
-            sr = link_sum ? sr + (tg[r] > 0 ? ls : C(0)) : sum9(f[r]);
+    if (mine) {
+        C sr = sum9(f[0]);
+        if (PULL && __any(tg[0] > 0)) {
+            const C ls = links(tg[0], f[0], ds, er);
+            sr = link_sum ? sr + (tg[0] > 0 ? ls : C(0)) : sum9(f[0]);
         }
-        put((ly + r * LY + 2) * RX + lx + 2, tg[r], sr);
+        put(0, sr);
     }
-#pragma unroll
-    for (int h = 0; h < NRL; ++h) {
-        if (link_sum) {
-            const C ls = Buf<C>::ld(rin, tgr[h] > 0 ? uint32_t(tgr[h] >> 8) * (REC2 * sc) + (RF2 + 8) * sc : OOB);
-            put(pr[h], tgr[h], sum9(fr[h]) + ls);
-        } else {
-            C d, e;
-            if (PULL && __any(tgr[h] > 0)) links(tgr[h], fr[h], d, e);
-            put(pr[h], tgr[h], sum9(fr[h]));
-        }
+    if (!SPLIT || !mine) {
+        C d, e;
+        if (PULL && !link_sum && __any(tg[KR] > 0)) links(tg[KR], f[KR], d, e);
+        put(KR, sum9(f[KR]) + ls_ring);
     }
     __syncthreads();
 
@@ -236,54 +237,57 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
     __syncthreads();
 
     // ---- 3: force, collision, store
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const bool out_node = x0 + lx < nx && y0 + ly + r * LY < ny;
-        const bool coll = out_node && tg[r] >= 0;
+    if (mine) {
+        const bool out_node = x0 + lx < nx && y0 + ly < ny;
+        const bool coll = out_node && tg[0] >= 0;
         MassAcc<S, C> rs_acc = 0;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) rs_acc += MassAcc<S, C>(f[r][i]);
-        rs_acc += MassAcc<S, C>(er[r]);  // what rounding kept out of f_0 (apply_links)
-        const C* P = s_psi + (ly + r * LY + 1) * PX + lx + 1;
+        for (int i = 0; i < 9; ++i) rs_acc += MassAcc<S, C>(f[0][i]);
+        rs_acc += MassAcc<S, C>(er);  // what rounding kept out of f_0 (apply_links)
+        const C* P = s_psi + (ly + 1) * PX + lx + 1;
         // F = -G psi(x) sum_i w^_i psi(x + e_i) e_i, w^ = 1/3 (axes), 1/12 (diagonals)
         const C gp = -a.G * P[0];
         const C Fx = gp * (C(1.0 / 3.0) * (P[1] - P[-1]) + C(1.0 / 12.0) * (P[PX + 1] - P[PX - 1] - P[-PX - 1] + P[-PX + 1]));
         const C Fy = gp * (C(1.0 / 3.0) * (P[PX] - P[-PX]) + C(1.0 / 12.0) * (P[PX + 1] + P[PX - 1] - P[-PX - 1] - P[-PX + 1]));
         C out[9];
         C rho, dux, duy, sx2, sy2, duu15;
-        collide9<S, C, MRT>(a, coll, f[r], rs_acc, Fx, Fy, out, rho, dux, duy, sx2, sy2, duu15);
-        const uint32_t x = uint32_t(y0 + ly + r * LY) * uint32_t(nx) + uint32_t(x0 + lx);
-        store_node<S, C>(false, rfb, rout, ns, out_node ? x * s : OOB, coll, tg[r], out, rho, dux, duy, sx2, sy2,
-                         duu15, ds[r]);
+        collide9<S, C, MRT>(a, coll, f[0], rs_acc, Fx, Fy, out, rho, dux, duy, sx2, sy2, duu15);
+        const uint32_t x = uint32_t(y0 + ly) * uint32_t(nx) + uint32_t(x0 + lx);
+        store_node<S, C>(false, rfb, rout, ns, out_node ? x * s : OOB, coll, tg[0], out, rho, dux, duy, sx2, sy2, duu15, ds);
     }
     if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
 }
 
-template <class S, class C, int TX, int NT, int RPL, int WPE>
+template <class S, class C, int TX, int NT, int OWN, int WPE>
 hipError_t launch_tile(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
-    constexpr int TY = NT / TX * RPL;
+    constexpr int TY = OWN / TX;
     Args2<S, C> a = step_args<S, C>(c, fcur, rcur, fnext, rnext);
     a.nsx = (a.nx + TX - 1) / TX;
     a.nblocks = a.nsx * ((a.ny + TY - 1) / TY);
     const bool mrt = c->p.collision == MCB_COLL_MRT;
-    const auto k = pull ? (mrt ? k_tile2d<S, C, TX, NT, RPL, WPE, true, true> : k_tile2d<S, C, TX, NT, RPL, WPE, true, false>)
-                        : (mrt ? k_tile2d<S, C, TX, NT, RPL, WPE, false, true> : k_tile2d<S, C, TX, NT, RPL, WPE, false, false>);
+    const auto k = pull ? (mrt ? k_tile2d<S, C, TX, NT, OWN, WPE, true, true> : k_tile2d<S, C, TX, NT, OWN, WPE, true, false>)
+                        : (mrt ? k_tile2d<S, C, TX, NT, OWN, WPE, false, true> : k_tile2d<S, C, TX, NT, OWN, WPE, false, false>);
     hipLaunchKernelGGL(k, dim3(unsigned(a.nblocks)), dim3(NT), 0, c->stream, a);
     return hipGetLastError();
 }
 
-// 32 x 8 tiles: one node and at most one ring node per lane, so that FP32 arithmetic fits 64 VGPRs (eight
-// waves per SIMD) and FP64 128 (four).  Wider tiles pull less ring (64 x 8 one pull in 2.2, 32 x 16 one
-// in 2.4, against one in 1.7) but run fewer waves or spill: 1024^2 FP32 21.6 us with 32 x 16 and 22.7 with
-// 64 x 16 against 20.8, FP64 38 and 44 against 35.6.  A box of fewer such tiles than half the
-// compute units takes 16 x 8 tiles of two waves, which spread it over twice as many units (64^2
-// FP64 5.3 us a step against 5.9, 128 x 160 5.6 against 6.2; at 256^2, one tile a unit, 7.1 against 6.7).
+// Large boxes: 32 x 8 tiles whose lanes pull one node and at most one ring node each, so that FP32 arithmetic
+// fits 64 VGPRs (eight waves per SIMD) and FP64 128 (four).  Wider tiles pull less ring (64 x 8 one pull in
+// 2.2, 32 x 16 one in 2.4, against one in 1.7) but run fewer waves or spill: 1024^2 FP32 21.6 us with 32 x
+// 16 and 22.7 with 64 x 16 against 20.8, FP64 38 and 44 against 35.6.
+// Boxes whose tiles are all resident at once wait for one chain of loads and dependent arithmetic, which is
+// shorter with lanes of their own for the ring: 256^2 FP64 7.0 -> 6.1 us a step, 400 x 300 8.5 -> 8.0, 512^2 FP32
+// 8.8 -> 8.0 (seven waves a tile: FP64 keeps two tiles a compute unit, FP32 four; past that they lose,
+// 512^2 FP64 12.4 -> 13.2, 724^2 FP32 12.7 -> 13.3).  Still smaller boxes take 8 x 8 tiles of three waves,
+// spread over four times as many units: 64^2 FP64 5.3 -> 4.4 us, 128 x 160 5.4 -> 5.2, 200^2 6.4 -> 5.9
+// (against 6.15 with 32 x 8 split; at 256^2, four tiles a unit, 6.3 against 6.1).
 template <class S, class C>
 hipError_t tile_t(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
-    constexpr int WPE = sizeof(C) == 8 ? 4 : 8;
-    const int64_t tiles = int64_t((c->p.nx + 31) / 32) * ((c->p.ny + 7) / 8);
-    if (2 * tiles < c->n_cu) return launch_tile<S, C, 16, 128, 1, WPE>(c, fcur, rcur, fnext, rnext, pull);
-    return launch_tile<S, C, 32, 256, 1, WPE>(c, fcur, rcur, fnext, rnext, pull);
+    auto tiles = [&](int tx, int ty) { return int64_t((c->p.nx + tx - 1) / tx) * ((c->p.ny + ty - 1) / ty); };
+    if (tiles(8, 8) <= 3 * c->n_cu) return launch_tile<S, C, 8, 192, 64, 4>(c, fcur, rcur, fnext, rnext, pull);
+    if (tiles(32, 8) <= (sizeof(C) == 8 ? 2 : 4) * c->n_cu)
+        return launch_tile<S, C, 32, 448, 256, 4>(c, fcur, rcur, fnext, rnext, pull);
+    return launch_tile<S, C, 32, 256, 256, sizeof(C) == 8 ? 4 : 8>(c, fcur, rcur, fnext, rnext, pull);
 }
 
 // ---------------------------------------------------------------- chemical-potential model
@@ -298,14 +302,16 @@ hipError_t tile_t(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, v
 //   4  mu of the tile and two nodes around it (eq. 12; solid nodes take their assigned values);
 //   5  force from both fields, eqs. 16-18 and the collision of the own nodes.
 // Measured against a march (one row per iteration, five barriers a row) that this replaces: 500 x 300
-// FP64 102 -> 14 us a step on a flat wall, 1024^2 FP32 on balls 144 -> 30, FP64 184 -> 55, 4096^2 FP32
+// FP64 102 -> 11 us a step on a flat wall, 1024^2 FP32 on balls 144 -> 30, FP64 184 -> 55, 4096^2 FP32
 // 483 -> 435, FP64 1048 -> 847.  Vector instructions bound it on large boxes.
-template <class S, class C, int TX, int NT, int RPL, int WPE, bool PULL, bool MRT>
+// Lanes t < OWN own the tile's nodes; where OWN < NT, ring entries go to the lanes past them first.
+template <class S, class C, int TX, int NT, int OWN, int RPL, int WPE, bool PULL, bool MRT>
 __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
-    constexpr int HC = 6, LY = NT / TX, TY = LY * RPL;
+    constexpr int HC = 6, LY = OWN / TX, TY = LY * RPL;
     constexpr int RX = TX + 2 * HC, RY = TY + 2 * HC, NR = RX * RY;
     constexpr int MX = TX + 4, MY = TY + 4, NM = MX * MY, NML = (NM + NT - 1) / NT;
     constexpr int NRING = NR - TX * TY, NRL = (NRING + NT - 1) / NT;
+    static_assert(OWN == NT || (RPL == 1 && NRL == 1 && OWN % 64 == 0), "lanes past the own ones make ring entries only");
     constexpr uint32_t s = sizeof(S), sc = sizeof(C);
     const Args2<S, C>& a = p.a;
     __shared__ C s_rho[NR];
@@ -326,6 +332,10 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
     }
     const int rq = rp / pw, x0 = (pan * a.H + rp - rq * pw) * TX, y0 = rq * TY;
     const int t = threadIdx.x, lx = t % TX, ly = t / TX, nx = a.nx, ny = a.ny;
+    // whether the lane owns nodes, its first ring entry, and whether its wave has any
+    const bool mine = OWN == NT || t < OWN;
+    const int jr = OWN == NT ? t : (t >= OWN ? t - OWN : t + NT - OWN);
+    const bool ring = OWN == NT || (jr & ~63) < NRING;
     const uint32_t n = uint32_t(nx) * uint32_t(ny), ns = n * s;
     const __amdgpu_buffer_rsrc_t rfa = res32(a.fa, 9u * ns), rfb = res32(a.fb, 9u * ns);
     const __amdgpu_buffer_rsrc_t rtag = res32(a.tag, n * 4u), rlay = res32(p.layer, n), rmu = res32(p.mu, n * sc);
@@ -341,6 +351,9 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
     // entries it makes, to serve their solid layers itself: entry | layer << 16, layer 3 where the
     // neighbours of a layer node do not all lie in the region (nothing reads those).
     int ent[RPL + NRL];
+    if (OWN != NT)
+#pragma unroll
+        for (int k = 0; k < RPL + NRL; ++k) ent[k] = 3 << 16;
     auto put = [&](int k, int rx, int ry, int g, int l, MassAcc<S, C> rs) {
         const int at = ry * RX + rx;
         s_rho[at] = g >= 0 ? C(rs) + a.rho_ref : C(0);
@@ -379,7 +392,7 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
         for (int k = 0; k < RPL + NRL; ++k) {
             int rx = lx + HC, ry = ly + k * LY + HC;
             if (k >= RPL) {
-                ring_at<TX, TY, HC>(min(t + (k - RPL) * NT, NRING - 1), rx, ry);
+                ring_at<TX, TY, HC>(min(jr + (k - RPL) * NT, NRING - 1), rx, ry);
                 px[k - RPL] = rx;
                 py[k - RPL] = ry;
             }
@@ -395,9 +408,11 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
             mus[h] = Buf<C>::ld(rmu, coord(j % MX + HC - 2, j / MX + HC - 2, mx, my) * sc);
         }
 #pragma unroll
-        for (int r = 0; r < RPL; ++r) pull_at<S, C, PULL, INNER>(rfa, cx[r], cy[r], nx, ny, f[r]);
+        for (int r = 0; r < RPL; ++r)
+            if (mine) pull_at<S, C, PULL, INNER>(rfa, cx[r], cy[r], nx, ny, f[r]);
 #pragma unroll
         for (int h = 0; h < NRL; ++h) {
+            if (!ring) break;
             C v[9], ls = C(0);
             pull_at<S, C, PULL, INNER>(rfa, cx[RPL + h], cy[RPL + h], nx, ny, v);
             if (link_sum) {
@@ -416,6 +431,7 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
     MassAcc<S, C> rs[RPL];  // what the collision hands back: the sum after eqs. 16-18
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
+        if (!mine) break;
         ds[r] = C(0);
         rs[r] = sum9(f[r]);
         MassAcc<S, C> rd = rs[r];
@@ -485,6 +501,7 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
     // ---- 5: force, collision, store
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
+        if (!mine) break;
         const bool out_node = x0 + lx < nx && y0 + ly + r * LY < ny;
         const bool coll = out_node && tg[r] >= 0;
         const C* R = s_rho + (ly + r * LY + HC) * RX + lx + HC;
@@ -502,9 +519,9 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
     if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
 }
 
-template <class S, class C, int TX, int NT, int RPL, int WPE>
+template <class S, class C, int TX, int NT, int OWN, int RPL, int WPE>
 hipError_t launch_cptile(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
-    constexpr int TY = NT / TX * RPL;
+    constexpr int TY = OWN / TX * RPL;
     ArgsCP<S, C> p = cp_args<S, C>(c, fcur, rcur, fnext, rnext);
     p.a.nsx = (p.a.nx + TX - 1) / TX;
     // Panels of 16 tiles: 4096^2 FP32 482 -> 451 us (1.16 -> 0.94 GB read), FP64 948 -> 872; 8, 32 and 64
@@ -519,12 +536,18 @@ hipError_t launch_cptile(mcb_ctx* c, const void* fcur, const void* rcur, void* f
     p.nt = bytes > (int64_t(1) << 28) && (sizeof(S) == 8 || (p.a.nx * int(sizeof(S))) % 128 == 0);
     p.a.nblocks = p.a.nsx * ((p.a.ny + TY - 1) / TY);
     const bool mrt = c->p.collision == MCB_COLL_MRT;
-    const auto k = pull ? (mrt ? k_cptile<S, C, TX, NT, RPL, WPE, true, true> : k_cptile<S, C, TX, NT, RPL, WPE, true, false>)
-                        : (mrt ? k_cptile<S, C, TX, NT, RPL, WPE, false, true> : k_cptile<S, C, TX, NT, RPL, WPE, false, false>);
+    const auto k = pull ? (mrt ? k_cptile<S, C, TX, NT, OWN, RPL, WPE, true, true> : k_cptile<S, C, TX, NT, OWN, RPL, WPE, true, false>)
+                        : (mrt ? k_cptile<S, C, TX, NT, OWN, RPL, WPE, false, true> : k_cptile<S, C, TX, NT, OWN, RPL, WPE, false, false>);
     hipLaunchKernelGGL(k, dim3(unsigned(p.a.nblocks)), dim3(NT), 0, c->stream, p);
     return hipGetLastError();
 }
 
+// A box whose tiles fit one per compute unit waits for one tile's chain of dependent loads and arithmetic:
+// the smallest tile that fits is taken, with lanes of their own for (nearly all of) its ring, which is three
+// to five times the tile in the small ones and is worked off in one pass with the tile instead of after
+// it.  FP64 on balls, against 32 x 16 tiles of 512 lanes: 64^2 13.0 -> 6.9 us a step, 128 x 160 14.7 -> 7.7,
+// 301 x 203 13.7 -> 10.0, 400 x 250 14.3 -> 11.9, 500 x 300 19.5 -> 14.3 (flat wall 14.5 -> 11.3), 512 x 384
+// 19.4 -> 15.3; 512^2, 24 rows a tile no longer one a unit, 20.5 -> 26.
 // 32 x 32 tiles of two nodes a lane pull 0.9 ring nodes per node, 32 x 16 tiles of one node a lane 1.4, but
 // run a shorter chain; the larger ones are taken once the box holds two of them per compute unit
 // (1024^2 FP64 58 us against 62, 2048 x 1024 FP32 52 against 56, 4096^2 FP32 480 against 534; 512^2 FP64,
@@ -534,9 +557,16 @@ hipError_t launch_cptile(mcb_ctx* c, const void* fcur, const void* rcur, void* f
 template <class S, class C>
 hipError_t cptile_t(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull) {
     constexpr int WPE = sizeof(C) == 8 ? 4 : 6;
-    const int64_t tiles = int64_t((c->p.nx + 31) / 32) * ((c->p.ny + 31) / 32);
-    if (tiles >= 2 * c->n_cu) return launch_cptile<S, C, 32, 512, 2, WPE>(c, fcur, rcur, fnext, rnext, pull);
-    return launch_cptile<S, C, 32, 512, 1, WPE>(c, fcur, rcur, fnext, rnext, pull);
+    auto tiles = [&](int tx, int ty) { return int64_t((c->p.nx + tx - 1) / tx) * ((c->p.ny + ty - 1) / ty); };
+    auto fits = [&](int tx, int ty) { return tiles(tx, ty) <= c->n_cu; };
+    if (tiles(32, 32) >= 2 * c->n_cu) return launch_cptile<S, C, 32, 512, 512, 2, WPE>(c, fcur, rcur, fnext, rnext, pull);
+    if (fits(8, 8)) return launch_cptile<S, C, 8, 448, 64, 1, 4>(c, fcur, rcur, fnext, rnext, pull);
+    if (fits(16, 8)) return launch_cptile<S, C, 16, 576, 128, 1, 4>(c, fcur, rcur, fnext, rnext, pull);
+    if (fits(16, 16)) return launch_cptile<S, C, 16, 768, 256, 1, 4>(c, fcur, rcur, fnext, rnext, pull);
+    if (fits(32, 16)) return launch_cptile<S, C, 32, 1024, 512, 1, 4>(c, fcur, rcur, fnext, rnext, pull);
+    if (fits(32, 20)) return launch_cptile<S, C, 32, 1024, 640, 1, 4>(c, fcur, rcur, fnext, rnext, pull);
+    if (fits(32, 24)) return launch_cptile<S, C, 32, 1024, 768, 1, 4>(c, fcur, rcur, fnext, rnext, pull);
+    return launch_cptile<S, C, 32, 512, 512, 1, WPE>(c, fcur, rcur, fnext, rnext, pull);
 }
 
 }  // namespace
