@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NT) void k_rho3f(Flat3<S, C> p) {
     // the wall nodes' psi reads the density of boundary nodes and of solid ones only
     if (tg != 0) p.rho[q.node] = r;
     p.psi[q.node] = tg >= 0 ? psi_val(r, a.eos, &bad) : C(0);
-    if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
+    raise_domain(bad, a.flags);
 }
 
 template <class S, class C>
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(NT) void k_psi3w(Flat3<S, C> p) {
     for (int i = 1; i < 19; ++i) num += w19<C>(i) * v[i];
     bool bad = false;
     p.psi[x] = psi_val(p.fac[w] * num, a.eos, &bad);
-    if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
+    raise_domain(bad, a.flags);
 }
 
 template <class S, class C, bool PULL>

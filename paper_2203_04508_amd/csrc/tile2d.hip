@@ -255,7 +255,7 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
         const uint32_t x = uint32_t(y0 + ly) * uint32_t(nx) + uint32_t(x0 + lx);
         store_node<S, C>(false, rfb, rout, ns, out_node ? x * s : OOB, coll, tg[0], out, rho, dux, duy, sx2, sy2, duu15, ds);
     }
-    if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
+    raise_domain(bad, a.flags);
 }
 
 template <class S, class C, int TX, int NT, int OWN, int WPE>
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
         store_node<S, C>(p.nt, rfb, rout, ns, out_node ? x * s : OOB, coll, tg[r], out, rho, dux, duy, sx2, sy2,
                          duu15, ds[r]);
     }
-    if (bad) atomicOr(&a.flags[FLAG_DOMAIN], 1);
+    raise_domain(bad, a.flags);
 }
 
 template <class S, class C, int TX, int NT, int OWN, int RPL, int WPE>
