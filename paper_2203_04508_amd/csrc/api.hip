@@ -1,6 +1,5 @@
 // Host side of the C ABI declared in include/mcb.h: argument checks, arena layout, call order,
-// stream handling and error reporting.  Device work lives in geometry.hip, step2d.hip,
-// step3d.hip and monitor.hip.
+// stream handling and error reporting.  Device work lives in the other .hip files of this folder.
 #include <algorithm>
 #include <cmath>
 #include <mutex>

@@ -100,9 +100,9 @@ def _pull_kernel(name):
     """The per-step kernels of the pulling step (not the collision that starts a run), by name:
     k_step2d<S, C, W, OUT, PULL>, k_step3d<S, C, PULL, PF>, k_rho3d<S, C, PULL>,
     k_rho3f<S, C, PULL, IBC>, k_collide3f<S, C, PULL> (and k_psi3w, which every step runs),
-    k_tile2d<S, C, TX, NT, RPL, WPE, PULL>, k_cptile<S, C, TX, NT, RPL, WPE, PULL>, and
+    k_tile2d<S, C, TX, NT, OWN, WPE, PULL>, k_cptile<S, C, TX, NT, OWN, RPL, WPE, PULL>, and
     k_cp_march<S, C, W, OUT, PULL> of older databases."""
-    for k, idx in (("k_step2d<", 4), ("k_step3d<", 2), ("k_rho3d<", 2), ("k_tile2d<", 6), ("k_cptile<", 6), ("k_cp_march<", 4),
+    for k, idx in (("k_step2d<", 4), ("k_step3d<", 2), ("k_rho3d<", 2), ("k_tile2d<", 6), ("k_cptile<", 7), ("k_cp_march<", 4),
                    ("k_rho3f<", 2), ("k_collide3f<", 2)):
         if k in name:
             args = name.split(k, 1)[1].split(">", 1)[0].split(",")
