@@ -1,5 +1,5 @@
-"""The transposed D2Q9 step's tile kernels (32 x 8 tiles, 32 x 16 in the chemical-potential model) on boxes that
-end inside, at and just past a tile, with walls across tile edges and round the periodic boundary;
+"""The transposed D2Q9 step's tile kernels on boxes that end inside, at and just past a tile of 8, 16 or 32
+columns, with walls across tile edges and round the periodic boundary;
 against the oracle's dual numbers, with the tolerance of the other reverse-mode tests (FP64 sums of a
 few hundred terms of one sign each: 1e-8 relative to the largest directional derivative)."""
 import numpy as np

@@ -1,6 +1,6 @@
 """The D2Q9 tile kernels (FP64 and FP32 boxes whose two lattices fit the memory-side cache; the
 chemical-potential model at every size) at the edges of their tiles
-(32 x 8 and, on boxes of few tiles, 16 x 8) and at boxes smaller than a tile, every storage type,
+(32 x 8 and, on boxes of few tiles, 8 x 8) and at boxes smaller than a tile, every storage type,
 boundary scheme and collision; and the row march on either side of the switch between the two, and for FP16 storage throughout.
 Against the FP64 oracle, with the per-step tolerances of the parity tests of each storage type
 (a handful of roundings of the storage format per step)."""
@@ -86,7 +86,7 @@ CP_EDGES = [(32, 16), (33, 17), (31, 33), (63, 15), (13, 70), (715, 730)]
 @pytest.mark.parametrize("prec", ["f64", "f32s", "f16s"])
 @pytest.mark.parametrize("dims", CP_EDGES, ids=lambda d: f"{d[0]}x{d[1]}")
 def test_chempot_tile_edges(mcb, dims, prec):
-    """Chemical-potential tiles: 32 x 16, and 32 x 32 on the last box (two of them per compute unit)."""
+    """Chemical-potential tiles: 8 x 8, and 32 x 32 on the last box (two of them per compute unit)."""
     print(f"\n[case] chempot {dims} {prec}", flush=True)
     rv, rl = W.PR_MAXWELL[0.80]
     T, T_cs = 0.80 * W.PR_TC, 0.7 * W.CS_TC
