@@ -143,6 +143,9 @@ hipError_t download(mcb_ctx* c, void* dst, const void* src, int64_t n) {
     }
     t.arrived_cv.notify_all();
     for (int k = 0; k < nth; ++k) th[k].join();
+    // after an error chunks may still be on their way into the ring: the next copy must not meet them, and
+    // where the stream cannot be waited for either, none uses the ring again
+    if (e != hipSuccess && hipStreamSynchronize(c->stream) != hipSuccess) ring_dev = -1;
     return e;
 }
 

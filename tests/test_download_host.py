@@ -1,0 +1,72 @@
+"""Host logic of csrc/download.hip (the copies to pageable host memory), built for the host against a stand-in for the
+runtime calls it makes (tests/hip_host): copies land only when something waits for them, and calls can
+be made to fail or to wait."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2203_04508_amd", "csrc")
+MB = 1 << 20
+
+
+@pytest.fixture()
+def lib(tmp_path):
+    so = str(tmp_path / "download_host.so")  # a library of its own for each test: the ring is a process-wide static
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-pthread", "-fno-gnu-unique", "-I", os.path.join(HERE, "hip_host"),
+                           "-I", CSRC, "-x", "c++", os.path.join(HERE, "hip_host", "download_host.cpp"), "-o", so])
+    L = C.CDLL(so)
+    for f in ("t_in_flight", "t_ring_copies"):
+        getattr(L, f).restype = C.c_int64
+    L.t_download.argtypes = [C.c_int, C.c_void_p, C.c_void_p, C.c_int64]
+    L.t_register.argtypes = [C.c_void_p, C.c_int]
+    L.t_reset(0, -1, 0)
+    return L
+
+
+def arrays(n, seed=0):
+    src = np.random.default_rng(seed).integers(0, 256, n, dtype=np.uint8)
+    return src, np.zeros(n, np.uint8)
+
+
+def copy(lib, k, dst, src):
+    return lib.t_download(k, dst.ctypes.data, src.ctypes.data, dst.size)
+
+
+def warm(lib, k=0):
+    """the ring is in use: a copy large enough for it"""
+    src, dst = arrays(128 * MB)
+    assert copy(lib, k, dst, src) == 0 and np.array_equal(dst, src)
+
+
+def test_whole(lib):
+    lib.t_open(0, 0)
+    warm(lib)
+    for n in (4 * MB - 1, 4 * MB, 5 * MB + 3, 33 * MB + 7):
+        src, dst = arrays(n, n)
+        assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
+    lib.t_close()
+    assert not lib.t_ring_there()
+
+
+def test_a_failed_copy_leaves_nothing_in_flight(lib):
+    """The ring's chunks that a failing copy had issued have landed before the next copy uses them."""
+    lib.t_open(0, 0)
+    warm(lib)
+    src, dst = arrays(64 * MB, 1)
+    lib.t_reset(0, 5, 0)
+    assert copy(lib, 0, dst, src) != 0
+    assert lib.t_in_flight() == 0
+    lib.t_reset(0, -1, 0)
+    assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
+    # where the stream cannot be waited for either, the ring is not used again
+    lib.t_reset(0, 5, 1)
+    assert copy(lib, 0, dst, src) != 0
+    lib.t_drop()
+    lib.t_reset(0, -1, 0)
+    assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
+    assert lib.t_ring_copies() == 0
+    lib.t_close()
