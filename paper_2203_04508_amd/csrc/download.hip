@@ -28,6 +28,7 @@ constexpr int WORKERS = 4;
 constexpr int R = 8;
 std::mutex ring_mu;   // held for the length of a copy
 char* ring = nullptr;
+std::mutex count_mu;  // its own, held for no copy: contexts come and go while another thread's copy runs
 int contexts = 0;
 
 hipEvent_t ring_ev[R];
@@ -150,13 +151,15 @@ hipError_t download(mcb_ctx* c, void* dst, const void* src, int64_t n) {
 }
 
 void download_open() {
-    std::lock_guard<std::mutex> l(ring_mu);
+    std::lock_guard<std::mutex> l(count_mu);
     ++contexts;
 }
 
 void download_close() {
-    std::lock_guard<std::mutex> l(ring_mu);
-    if (--contexts == 0) ring_free();
+    std::lock_guard<std::mutex> l(count_mu);
+    if (--contexts > 0) return;
+    std::lock_guard<std::mutex> r(ring_mu);  // free: a copy belongs to a context, and there is none
+    ring_free();
 }
 
 }  // namespace mcb

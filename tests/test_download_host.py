@@ -4,6 +4,7 @@ be made to fail or to wait."""
 import ctypes as C
 import os
 import subprocess
+import threading
 
 import numpy as np
 import pytest
@@ -70,3 +71,27 @@ def test_a_failed_copy_leaves_nothing_in_flight(lib):
     assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
     assert lib.t_ring_copies() == 0
     lib.t_close()
+
+
+def test_contexts_come_and_go_during_a_copy(lib):
+    """Creating and destroying a context does not wait for another thread's copy."""
+    lib.t_open(0, 0)
+    warm(lib)
+    src, dst = arrays(64 * MB, 2)
+    lib.t_hold(1)
+    rc = []
+    a = threading.Thread(target=lambda: rc.append(copy(lib, 0, dst, src)))
+    a.start()
+    lib.t_wait_held()
+    b = threading.Thread(target=lambda: (lib.t_open(1, 0), lib.t_close()))
+    b.start()
+    b.join(10.0)
+    stuck = b.is_alive()
+    lib.t_hold(0)
+    a.join()
+    b.join()
+    assert not stuck
+    assert rc == [0] and np.array_equal(dst, src)
+    assert lib.t_ring_there()
+    lib.t_close()
+    assert not lib.t_ring_there()
