@@ -63,6 +63,15 @@ hipError_t plain(mcb_ctx* c, void* dst, const void* src, int64_t n) {
     return e != hipSuccess ? e : hipStreamSynchronize(c->stream);
 }
 
+// Whether the runtime knows the destination.  Pinned memory it writes at the link's rate (28.8 MB 0.60 ms
+// against 0.99 through the ring, 402 MB 7.8 against 10.7), and what is not plain host memory is its alone.
+bool known(const void* dst) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, dst) == hipSuccess) return a.type != hipMemoryTypeUnregistered;
+    (void)hipGetLastError();
+    return false;
+}
+
 // The ring's slot of chunk i is i % R.  A worker claims the next chunk, waits until it has arrived,
 // copies it out and frees its slot; the calling thread issues the device copies, each into a freed
 // slot, and marks the chunks that have arrived.  Every wait ends: a chunk arrives once its slot is
@@ -98,7 +107,7 @@ struct Transfer {
 
 hipError_t download(mcb_ctx* c, void* dst, const void* src, int64_t n) {
     // below 4 MB the runtime's copy is as fast as starting the threads
-    if (n < (int64_t(4) << 20)) return plain(c, dst, src, n);
+    if (n < (int64_t(4) << 20) || known(dst)) return plain(c, dst, src, n);
     std::unique_lock<std::mutex> mine(ring_mu, std::try_to_lock);
     if (!mine.owns_lock() || !ring_ready(c->device)) return plain(c, dst, src, n);
     Transfer t;

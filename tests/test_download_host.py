@@ -95,3 +95,16 @@ def test_contexts_come_and_go_during_a_copy(lib):
     assert lib.t_ring_there()
     lib.t_close()
     assert not lib.t_ring_there()
+
+
+@pytest.mark.parametrize("kind", [1, 2, 3], ids=["pinned", "device", "managed"])
+def test_memory_the_runtime_knows_is_written_by_it(lib, kind):
+    """A destination that is pinned (or no plain host memory at all) takes one copy, without the ring."""
+    lib.t_open(0, 0)
+    warm(lib)
+    src, dst = arrays(64 * MB, 3)
+    lib.t_register(dst.ctypes.data, kind)
+    lib.t_reset(0, -1, 0)
+    assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
+    assert lib.t_ring_copies() == 0
+    lib.t_close()
