@@ -41,6 +41,9 @@ void ring_free() {
 }
 
 bool ring_ready(int dev) {  // with ring_mu held
+    // the context's device has to be current, for the events and for a null stream alike
+    int cur = -1;
+    if (hipGetDevice(&cur) != hipSuccess || cur != dev) return false;
     if (ring) return dev == ring_dev;
     void* p = nullptr;
     hipError_t e = hipHostMalloc(&p, size_t(CHUNK * R), hipHostMallocDefault);

@@ -108,3 +108,20 @@ def test_memory_the_runtime_knows_is_written_by_it(lib, kind):
     assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
     assert lib.t_ring_copies() == 0
     lib.t_close()
+
+
+def test_another_device_is_current(lib):
+    """Events belong to the current device: a caller that has another one current takes the runtime's copy, and no
+    ring is made for it."""
+    lib.t_open(0, 0)
+    src, dst = arrays(128 * MB, 4)
+    lib.t_reset(1, -1, 0)
+    assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
+    assert lib.t_ring_copies() == 0 and not lib.t_ring_there()
+    lib.t_reset(0, -1, 0)
+    warm(lib)
+    assert lib.t_ring_copies() > 0
+    lib.t_reset(1, -1, 0)
+    assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
+    assert lib.t_ring_copies() == 0
+    lib.t_close()
