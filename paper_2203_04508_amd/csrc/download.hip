@@ -22,14 +22,19 @@ namespace {
 constexpr int64_t CHUNK = int64_t(2) << 20;
 constexpr int WORKERS = 4;
 
-// The ring of pinned chunks (16 MB), one for the process: a lattice's copies are rare against its steps, and
-// pinning costs about a quarter of a millisecond per megabyte.  Made by the first large copy, used by one
-// copy at a time (a copy that finds it taken goes the runtime's way), given back with the last context.
+// The ring of pinned chunks (16 MB), one for the process: a lattice's copies are rare against its steps.  Used by
+// one copy at a time (a copy that finds it taken goes the runtime's way), given back with the last context.
 constexpr int R = 8;
 std::mutex ring_mu;   // held for the length of a copy
 char* ring = nullptr;
 std::mutex count_mu;  // its own, held for no copy: contexts come and go while another thread's copy runs
 int contexts = 0;
+
+// Pinning takes 2 ms and a copy through the ring saves 25 us a megabyte into arrays in use, 50 into fresh ones:
+// it is made once RING_AFTER bytes have been asked for in large copies, this one included, since there were
+// contexts (made by the first large copy, it cost the first report of 800 x 700 nodes 2.9 ms instead of 1.3).
+constexpr int64_t RING_AFTER = int64_t(48) << 20;
+int64_t asked = 0;  // with ring_mu held
 
 hipEvent_t ring_ev[R];
 int ring_events = 0, ring_dev = -1;  // events belong to the device that was current when the ring was made
@@ -112,7 +117,12 @@ hipError_t download(mcb_ctx* c, void* dst, const void* src, int64_t n) {
     // below 4 MB the runtime's copy is as fast as starting the threads
     if (n < (int64_t(4) << 20) || known(dst)) return plain(c, dst, src, n);
     std::unique_lock<std::mutex> mine(ring_mu, std::try_to_lock);
-    if (!mine.owns_lock() || !ring_ready(c->device)) return plain(c, dst, src, n);
+    if (!mine.owns_lock()) return plain(c, dst, src, n);
+    asked += n;
+    if (asked < RING_AFTER || !ring_ready(c->device)) {
+        mine.unlock();
+        return plain(c, dst, src, n);
+    }
     Transfer t;
     t.nch = (n + CHUNK - 1) / CHUNK;
     std::thread th[WORKERS];
@@ -172,6 +182,7 @@ void download_close() {
     if (--contexts > 0) return;
     std::lock_guard<std::mutex> r(ring_mu);  // free: a copy belongs to a context, and there is none
     ring_free();
+    asked = 0;
 }
 
 }  // namespace mcb

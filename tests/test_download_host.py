@@ -125,3 +125,19 @@ def test_another_device_is_current(lib):
     assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
     assert lib.t_ring_copies() == 0
     lib.t_close()
+
+
+def test_the_ring_is_pinned_once_it_pays(lib):
+    """A process that copies little never pays for the pinning; one that copies on does so once."""
+    lib.t_open(0, 0)
+    src, dst = arrays(12 * MB, 5)
+    for k in range(6):
+        lib.t_reset(0, -1, 0)
+        assert copy(lib, 0, dst, src) == 0 and np.array_equal(dst, src)
+        # 48 MB in all: the fourth copy reaches it
+        assert bool(lib.t_ring_there()) == (k >= 3) and (lib.t_ring_copies() > 0) == (k >= 3), k
+    lib.t_close()
+    assert not lib.t_ring_there()
+    lib.t_open(0, 0)
+    assert copy(lib, 0, dst, src) == 0 and not lib.t_ring_there()
+    lib.t_close()
