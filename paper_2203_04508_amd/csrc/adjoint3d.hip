@@ -50,6 +50,12 @@ __device__ __forceinline__ void stencil3(const double (&v)[19], double (&s)[3]) 
     s[1] = wa * (v[3] - v[4]) + we * (exy1 - exy2 + eyz1 + eyz2);
     s[2] = wa * (v[5] - v[6]) + we * (exz1 - exz2 + eyz1 - eyz2);
 }
+// sum of f_i e_i
+__device__ __forceinline__ void momentum(const double (&f)[19], double (&j)[3]) {
+    j[0] = (f[1] - f[2]) + (f[7] - f[8]) + (f[9] - f[10]) + (f[11] - f[12]) + (f[13] - f[14]);
+    j[1] = (f[3] - f[4]) + (f[7] - f[8]) - (f[9] - f[10]) + (f[15] - f[16]) + (f[17] - f[18]);
+    j[2] = (f[5] - f[6]) + (f[11] - f[12]) - (f[13] - f[14]) + (f[15] - f[16]) - (f[17] - f[18]);
+}
 // sum over k of w_k e_k . H(x - e_k), w the weights of the force stencil; nb: the neighbours x + e_i
 __device__ __forceinline__ double gather_H(const AdjDev& A, const double* __restrict__ H, const uint32_t (&nb)[19]) {
     const int64_t N = A.g.N;
@@ -95,15 +101,26 @@ __global__ __launch_bounds__(NT) void k_adj3_pre(Adj3 p, const S* __restrict__ g
             f[i] = kMixed<S> && i == 0 ? double(ldo(reinterpret_cast<const float*>(gt), q.node * 4u))
                                        : double(ldo(gt + plane_off<S>(i, N), nb[opp<1>(i)] * uint32_t(sizeof(S))));
         if (__any(tg > 0)) {
-            // eqs. 16-18 from the boundary record: rho, du = F / rho, 2u + du, 1.5 du.(2u + du) and the
-            // node's own populations
+            // eqs. 16-18.  The forcing terms are those of the stored state, in FP64: density and momentum from
+            // the node's own populations, the force from its record (F = rho du; the collision left j + F)
             RC h[RF3 + 18];
             double a[18];
             ld_vec(make_res(rec, uint64_t(p.A.nb) * REC3 * sizeof(RC)),
                    tg > 0 ? uint32_t(tg - 1) * uint32_t(REC3 * sizeof(RC)) : OOB, h);
             coefs(la, p.A.nb, tg, a);
-            const double kr = A.kF * double(h[0]), dx = double(h[1]), dy = double(h[2]), dz = double(h[3]);
-            const double sx = double(h[4]), sy = double(h[5]), sz = double(h[6]), duu = double(h[7]);
+            double own[19];
+            own[0] = f[0];
+#pragma unroll
+            for (int i = 1; i < 19; ++i) own[i] = double(h[RF3 + i - 1]);
+            double ro = A.rho_ref, m[3];
+#pragma unroll
+            for (int i = 0; i < 19; ++i) ro += own[i];
+            momentum(own, m);
+            const double ir = 1.0 / ro, kr = A.kF * ro, rr = double(h[0]);
+            const double Fx = rr * double(h[1]), Fy = rr * double(h[2]), Fz = rr * double(h[3]);
+            const double dx = Fx * ir, dy = Fy * ir, dz = Fz * ir;
+            const double sx = 2.0 * (m[0] - Fx) * ir + dx, sy = 2.0 * (m[1] - Fy) * ir + dy, sz = 2.0 * (m[2] - Fz) * ir + dz;
+            const double duu = 1.5 * (dx * sx + dy * sy + dz * sz);
             double dm = 0.0;
             // a slot that a link replaces is never one that an eq. 16 link reads
 #pragma unroll
@@ -124,9 +141,7 @@ __global__ __launch_bounds__(NT) void k_adj3_pre(Adj3 p, const S* __restrict__ g
         r = A.rho_ref;
 #pragma unroll
         for (int i = 0; i < 19; ++i) r += f[i];
-        j[0] = (f[1] - f[2]) + (f[7] - f[8]) + (f[9] - f[10]) + (f[11] - f[12]) + (f[13] - f[14]);
-        j[1] = (f[3] - f[4]) + (f[7] - f[8]) - (f[9] - f[10]) + (f[15] - f[16]) + (f[17] - f[18]);
-        j[2] = (f[5] - f[6]) + (f[11] - f[12]) - (f[13] - f[14]) + (f[15] - f[16]) - (f[17] - f[18]);
+        momentum(f, j);
     } else {
         r = ldo(p.w.rho0, q.node * 8u);
     }
