@@ -94,9 +94,10 @@ __device__ __forceinline__ void ring_at(int j, int& rx, int& ry) {
 // Three phases, two barriers:
 //   1  every node of the tile and of the ring two nodes wide around it is pulled by one lane (psi of the
 //      ring next to the tile needs, through the wall nodes, the density two nodes out); eqs. 16-18 are
-//      applied to the tile's own, and the densities of the (TX + 4) x (TY + 4) region go to LDS: a wall
-//      node's entry is minus its eq. 15 factor, any other solid node's is zero.  Lanes past the own ones pull
-//      the ring (OWN < NT), or the own lanes pull a node of it too (OWN = NT);
+//      applied to the tile's own, and the densities of the (TX + 4) x (TY + 4) region go to LDS, zero on
+//      solid nodes; the place of psi holds what it takes: a wall node's eq. 15 factor, zero on other solid
+//      nodes, -1 on fluid ones.  Lanes past the own ones pull the ring (OWN < NT), or the own lanes pull
+//      a node of it too (OWN = NT);
 //   2  psi of the (TX + 2) x (TY + 2) region, wall nodes from the entries around them (eq. 15);
 //   3  force, collision, store and boundary record of the own nodes, whose populations stayed in
 //      registers.
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
     constexpr int NP = PX * PY, NPL = (NP + NT - 1) / NT;
     constexpr uint32_t s = sizeof(S), sc = sizeof(C);
     __shared__ C s_rho[RY * RX];
-    __shared__ C s_psi[PY * PX];
+    __shared__ C s_psi[RY * RX];
     // XCD-aware order: consecutive tiles go to the same XCD (one L2)
     const int bid = blockIdx.x;
     const int per = a.nblocks >> 3, rem = a.nblocks & 7;
@@ -189,10 +190,10 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
     if (link_sum && (!SPLIT || !mine))
         ls_ring = Buf<C>::ld(rin, tg[KR] > 0 ? uint32_t(tg[KR] >> 8) * (REC2 * sc) + (RF2 + 8) * sc : OOB);
     auto put = [&](int k, C sr) {
-        const C rho = sr + a.rho_ref;
         const int g = tg[k];
-        if (!(g >= 0 ? rho > C(0) : (g == -1 || fac[k] > C(0)))) bad = true;  // the signs carry meaning below
-        s_rho[at[k]] = g >= 0 ? rho : (g == -1 ? C(0) : -fac[k]);
+        if (g <= -2 && !(fac[k] > C(0))) bad = true;  // its sign carries meaning below
+        s_rho[at[k]] = g >= 0 ? sr + a.rho_ref : C(0);
+        s_psi[at[k]] = g >= 0 ? C(-1) : fac[k];  // (0 on solid nodes that are no wall nodes)
     };
     if (mine) {
         C sr = sum9(f[0]);
@@ -215,9 +216,9 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
         const int j = t + h * NT;
         if (j < NP) {
             const int c = (j / PX + 1) * RX + j % PX + 1;
-            const C rc = s_rho[c];
-            C rn = rc;
-            if (rc < C(0)) {
+            const C fw = s_psi[c];
+            C rn = s_rho[c];
+            if (fw > C(0)) {
                 // wall node: the weighted sum of its fluid neighbours' densities times the factor
                 C num = C(0);
 #pragma unroll
@@ -226,12 +227,11 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
                     for (int dx = -1; dx <= 1; ++dx) {
                         if (dx == 0 && dy == 0) continue;
                         const C w = (dx == 0 || dy == 0) ? C(1.0 / 9.0) : C(1.0 / 36.0);
-                        const C v = s_rho[c + dy * RX + dx];
-                        num += w * (v > C(0) ? v : C(0));
+                        num += w * s_rho[c + dy * RX + dx];
                     }
-                rn = -rc * num;
+                rn = fw * num;
             }
-            s_psi[j] = rc == C(0) ? C(0) : psi_val(rn, a.eos, &bad);
+            s_psi[c] = fw == C(0) ? C(0) : psi_val(rn, a.eos, &bad);
         }
     }
     __syncthreads();
@@ -244,11 +244,11 @@ __global__ __launch_bounds__(NT, WPE) void k_tile2d(Args2<S, C> a) {
 #pragma unroll
         for (int i = 0; i < 9; ++i) rs_acc += MassAcc<S, C>(f[0][i]);
         rs_acc += MassAcc<S, C>(er);  // what rounding kept out of f_0 (apply_links)
-        const C* P = s_psi + (ly + 1) * PX + lx + 1;
+        const C* P = s_psi + (ly + 2) * RX + lx + 2;
         // F = -G psi(x) sum_i w^_i psi(x + e_i) e_i, w^ = 1/3 (axes), 1/12 (diagonals)
         const C gp = -a.G * P[0];
-        const C Fx = gp * (C(1.0 / 3.0) * (P[1] - P[-1]) + C(1.0 / 12.0) * (P[PX + 1] - P[PX - 1] - P[-PX - 1] + P[-PX + 1]));
-        const C Fy = gp * (C(1.0 / 3.0) * (P[PX] - P[-PX]) + C(1.0 / 12.0) * (P[PX + 1] + P[PX - 1] - P[-PX - 1] - P[-PX + 1]));
+        const C Fx = gp * (C(1.0 / 3.0) * (P[1] - P[-1]) + C(1.0 / 12.0) * (P[RX + 1] - P[RX - 1] - P[-RX - 1] + P[-RX + 1]));
+        const C Fy = gp * (C(1.0 / 3.0) * (P[RX] - P[-RX]) + C(1.0 / 12.0) * (P[RX + 1] + P[RX - 1] - P[-RX - 1] - P[-RX + 1]));
         C out[9];
         C rho, dux, duy, sx2, sy2, duu15;
         collide9<S, C, MRT>(a, coll, f[0], rs_acc, Fx, Fy, out, rho, dux, duy, sx2, sy2, duu15);
