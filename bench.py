@@ -25,7 +25,7 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-from paper_2203_04508_amd.roofline import HBM_PEAK_GBS, STORAGE_BYTES, algorithmic_bytes, layout_bytes  # noqa: E402
+from paper_2203_04508_amd.roofline import HBM_PEAK_GBS, STORAGE_BYTES, algorithmic_bytes, layout_bytes, step_kernels  # noqa: E402
 
 METRIC = "MLUPS & % HBM roofline per step; fwd+adjoint MLUPS; relative mass drift"
 DTYPES = {"f64": "f64", "f32s": "f32", "f16s": "f32"}
@@ -267,8 +267,7 @@ def main():
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": ("k_cptile (one step)" if args.model == "chempot"
-                       else "k_step2d" if wl.dim == 2 else "k_rho3f + k_psi3w + k_collide3f (one step)"),
+            "kernel": step_kernels(wl, args.precision, args.model),
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

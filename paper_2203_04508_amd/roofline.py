@@ -29,3 +29,17 @@ def layout_bytes(wl, precision, nb):
     rec, nlk = (mcb.REC2, mcb.Q2_LINKS) if wl.dim == 2 else (mcb.REC3, mcb.Q3_LINKS)
     planes = wl.Q + 1 if precision == "f16s" else wl.Q
     return wl.N * (2 * planes * s + 4) + nb * (2 * rec + nlk) * cb
+
+
+# the library's TILE_BYTES (csrc/mcb_internal.h): up to here a D2Q9 pseudopotential step runs in tiles
+TILE_BYTES = 240_000_000
+
+
+def step_kernels(wl, precision, model="pseudo"):
+    """The kernels that one step of a lattice runs in, as the library chooses them."""
+    half = precision == "f16s"
+    if wl.dim == 3:
+        return ("k_rho3d + k_step3d" if half else "k_rho3f + k_psi3w + k_collide3f") + " (one step)"
+    if model == "chempot":
+        return ("k_cp_march" if half else "k_cptile") + " (one step)"
+    return "k_step2d" if half or 2 * wl.N * wl.Q * STORAGE_BYTES[precision] > TILE_BYTES else "k_tile2d"
