@@ -33,13 +33,6 @@ __device__ __forceinline__ void eadd(int i, double v, double (&acc)[2]) {
     if (kEy[i] != 0) acc[1] += kEy[i] > 0 ? v : -v;
 }
 
-// periodic image of a coordinate
-__device__ __forceinline__ int image(int v, int m) {
-    while (v < 0) v += m;
-    while (v >= m) v -= m;
-    return v;
-}
-
 // the tile of a workgroup, consecutive tiles on the same XCD
 struct Tile {
     int x0, y0;
@@ -49,15 +42,6 @@ __device__ __forceinline__ Tile tile_of(int nsx) {
     const int nb = gridDim.x, bid = blockIdx.x, per = nb >> 3, rem = nb & 7, xcd = bid & 7, k8 = bid >> 3;
     const int l = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + k8;
     return {(l % nsx) * TX, (l / nsx) * TY};
-}
-
-// entry j of the ring of H nodes around a TX x TY tile, in the coordinates of the region of tile and ring
-template <int TX, int TY, int H>
-__device__ __forceinline__ void ring_at(int j, int& rx, int& ry) {
-    constexpr int RX = TX + 2 * H;
-    const int q = j - 2 * H * RX;
-    ry = q < 0 ? (j < H * RX ? j / RX : TY + j / RX) : q / (2 * H) + H;
-    rx = q < 0 ? j % RX : (q % (2 * H) < H ? q % (2 * H) : TX + q % (2 * H));
 }
 
 // populations arriving at node (cx, cy) of a state (eq. 5, from x - e_i), as stored: less w rho_ref, which drops

@@ -273,6 +273,24 @@ __device__ inline C psi_of(C rho, const Eos<C>& e, int32_t* flags) {
     return fsqrt(arg);
 }
 
+// periodic image of a coordinate (at most one addition or subtraction unless the box is smaller than
+// a tile and its ring)
+__device__ __forceinline__ int image(int v, int m) {
+    while (v < 0) v += m;
+    while (v >= m) v -= m;
+    return v;
+}
+
+// Entry j of the ring of H nodes around a TX x TY tile, in the coordinates of the (TX + 2 H) x (TY + 2 H)
+// region: H rows below, H above, then H columns on either side of each tile row.
+template <int TX, int TY, int H>
+__device__ __forceinline__ void ring_at(int j, int& rx, int& ry) {
+    constexpr int RX = TX + 2 * H;
+    const int q = j - 2 * H * RX;
+    ry = q < 0 ? (j < H * RX ? j / RX : TY + j / RX) : q / (2 * H) + H;
+    rx = q < 0 ? j % RX : (q % (2 * H) < H ? q % (2 * H) : TX + q % (2 * H));
+}
+
 __device__ inline int wrap1(int a, int n) { return a < 0 ? a + n : (a >= n ? a - n : a); }
 
 }  // namespace mcb

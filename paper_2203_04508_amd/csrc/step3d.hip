@@ -41,6 +41,20 @@ constexpr int NRL = (NR + NT - 1) / NT, NPL = (NP + NT - 1) / NT;  // region ent
 
 // ================================================================ density pass
 
+template <class S, class C>
+struct RhoArgs {
+    const S* fa;                 // post-collision populations of time t, SoA [19][N]
+    const int32_t* tag;          // >0: boundary index + 1; 0 fluid; -1 solid; -2-w wall w
+    const C* rin;                // boundary records of time t
+    const C* la;                 // link coefficients, Q3_LINKS per boundary node (IBC only)
+    const C* fac;                // eq. 15 factor per wall node
+    C* rho;                      // out, per node
+    int32_t* flags;
+    int nx, ny, nz, nbx;
+    C rho_ref;
+    int ibc;                     // boundary scheme without eq. 18: links' f_in summed explicitly
+};
+
 // One lane per node, workgroups of 256 consecutive nodes of an x-row.  PULL = false sums the
 // node's own populations (the collision that starts a run).
 template <class S, class C, bool PULL>
@@ -152,7 +166,7 @@ __device__ __forceinline__ void ld_rec(const March3<S, C>& M, int tg, C (&rec)[R
     ld_vec(M.la, tg > 0 ? bi * (Q3_LINKS * sc) : OOB, ca);
 }
 
-template <class S, class C, bool PULL, bool PF>
+template <class S, class C, bool PULL>
 __global__ __launch_bounds__(NT) void k_step3d(Args3<S, C> a) {
     // XCD-aware order: consecutive logical tiles (neighbours in x) go to the same XCD (one L2)
     const int bid = blockIdx.x;
@@ -270,9 +284,8 @@ __global__ __launch_bounds__(NT) void k_step3d(Args3<S, C> a) {
             C dsC = C(0);
             C erC = C(0);
             if (PULL && __any(tgC > 0)) {
-                // without the prefetch (FP64) the record and the coefficients are loaded here
                 const uint32_t bi = uint32_t(tgC - 1);
-                dsC = apply_links3<S, C, !PF>(tgC > 0, recC, aC, fC, M.rin, tgC > 0 ? bi * (REC3 * sc) : OOB, M.la,
+                dsC = apply_links3<S, C, false>(tgC > 0, recC, aC, fC, M.rin, tgC > 0 ? bi * (REC3 * sc) : OOB, M.la,
                                               tgC > 0 ? bi * (Q3_LINKS * sc) : OOB, a.kF, a.k18, erC);
             }
             C out[19];
@@ -381,19 +394,17 @@ __global__ __launch_bounds__(NT) void k_step3d(Args3<S, C> a) {
                 st_vec(M.rout, (coll && tgC > 0) ? uint32_t(tgC - 1) * (REC3 * sc) : OOB, rv);
             }
         }
-        // ---- boundary record and link coefficients of plane p + 1 (PF), issued once those of plane
+        // ---- boundary record and link coefficients of plane p + 1, issued once those of plane
         // p are used up, only by waves that hold a boundary node in it
-        if (PF && PULL && __any(tgN > 0)) ld_rec(M, tgN, recN, aN);
+        if (PULL && __any(tgN > 0)) ld_rec(M, tgN, recN, aN);
         if (__any(tgN > 0)) mkN = uint32_t(ld_i32(M.nmask, tgN > 0 ? M.own4 : OOB, uint32_t(zqm) * M.p4));
         // plane p + 1 becomes plane p
 #pragma unroll
         for (int i = 0; i < 19; ++i) fC[i] = fN[i];
-        if (PF) {
 #pragma unroll
-            for (int i = 0; i < RF3 + 18; ++i) recC[i] = recN[i];
+        for (int i = 0; i < RF3 + 18; ++i) recC[i] = recN[i];
 #pragma unroll
-            for (int i = 0; i < 18; ++i) aC[i] = aN[i];
-        }
+        for (int i = 0; i < 18; ++i) aC[i] = aN[i];
         tgC = tgN;
         tgN = tgNN;
         mkC = mkN;
@@ -436,10 +447,9 @@ hipError_t launch_step3d(mcb_ctx* c, const void* fcur, const void* rcur, void* f
     // 256^3): the planes in flight then spread over the lattice instead of marching in step, which
     // measured faster here than deep segments or a single resident round; the ring of four extra
     // density planes per segment costs one value per node each
-    constexpr bool PF = sizeof(C) == 4;
     int* occ = c->occ + 4;  // slots 4, 5 (a context runs one storage type)
-    const int cap = pull ? resident_blocks(c, k_step3d<S, C, true, PF>, NT, &occ[1])
-                         : resident_blocks(c, k_step3d<S, C, false, PF>, NT, &occ[0]);
+    const int cap = pull ? resident_blocks(c, k_step3d<S, C, true>, NT, &occ[1])
+                         : resident_blocks(c, k_step3d<S, C, false>, NT, &occ[0]);
     const int64_t tiles = int64_t(a.ntx) * a.nty;
     const int64_t per = 12 * cap / tiles > 0 ? 12 * cap / tiles : 1;  // segments per tile column
     int D = int((a.nz + per - 1) / per);
@@ -447,9 +457,9 @@ hipError_t launch_step3d(mcb_ctx* c, const void* fcur, const void* rcur, void* f
     a.D = D;
     a.nblocks = a.ntx * a.nty * ((a.nz + D - 1) / D);
     if (pull)
-        hipLaunchKernelGGL((k_step3d<S, C, true, PF>), dim3(a.nblocks), dim3(NT), 0, c->stream, a);
+        hipLaunchKernelGGL((k_step3d<S, C, true>), dim3(a.nblocks), dim3(NT), 0, c->stream, a);
     else
-        hipLaunchKernelGGL((k_step3d<S, C, false, PF>), dim3(a.nblocks), dim3(NT), 0, c->stream, a);
+        hipLaunchKernelGGL((k_step3d<S, C, false>), dim3(a.nblocks), dim3(NT), 0, c->stream, a);
     return hipGetLastError();
 }
 

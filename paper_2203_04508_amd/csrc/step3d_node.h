@@ -74,20 +74,6 @@ __device__ __forceinline__ void neighbours(const Node3& p, int nx, int ny, int n
 __device__ constexpr int opp3(int i) { return i == 0 ? 0 : ((i & 1) ? i + 1 : i - 1); }
 
 template <class S, class C>
-struct RhoArgs {
-    const S* fa;                 // post-collision populations of time t, SoA [19][N]
-    const int32_t* tag;          // >0: boundary index + 1; 0 fluid; -1 solid; -2-w wall w
-    const C* rin;                // boundary records of time t
-    const C* la;                 // link coefficients, Q3_LINKS per boundary node (IBC only)
-    const C* fac;                // eq. 15 factor per wall node
-    C* rho;                      // out, per node
-    int32_t* flags;
-    int nx, ny, nz, nbx;
-    C rho_ref;
-    int ibc;                     // boundary scheme without eq. 18: links' f_in summed explicitly
-};
-
-template <class S, class C>
 struct Args3 {
     const S* fa;                 // post-collision populations of time t, SoA [19][N]
     S* fb;                       // post-collision populations of time t+1

@@ -71,24 +71,6 @@ __device__ __forceinline__ void store_node(bool nt, __amdgpu_buffer_rsrc_t fb, _
     }
 }
 
-// periodic image of a coordinate (at most one addition or subtraction unless the box is smaller than
-// a tile and its ring)
-__device__ __forceinline__ int image(int v, int m) {
-    while (v < 0) v += m;
-    while (v >= m) v -= m;
-    return v;
-}
-
-// Entry j of the ring of H nodes around a TX x TY tile, in the coordinates of the (TX + 2 H) x (TY + 2 H)
-// region: H rows below, H above, then H columns on either side of each tile row.
-template <int TX, int TY, int H>
-__device__ __forceinline__ void ring_at(int j, int& rx, int& ry) {
-    constexpr int RX = TX + 2 * H;
-    const int q = j - 2 * H * RX;
-    ry = q < 0 ? (j < H * RX ? j / RX : TY + j / RX) : q / (2 * H) + H;
-    rx = q < 0 ? j % RX : (q % (2 * H) < H ? q % (2 * H) : TX + q % (2 * H));
-}
-
 // ---------------------------------------------------------------- pseudopotential model
 // A workgroup owns a tile of TX x TY nodes, TY = OWN / TX; lane t < OWN owns column t % TX of row t / TX.
 // Three phases, two barriers:

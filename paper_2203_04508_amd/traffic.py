@@ -98,7 +98,7 @@ def _largest(rows, match):
 
 def _pull_kernel(name):
     """The per-step kernels of the pulling step (not the collision that starts a run), by name:
-    k_step2d<S, C, W, OUT, PULL>, k_step3d<S, C, PULL, PF>, k_rho3d<S, C, PULL>,
+    k_step2d<S, C, W, OUT, PULL>, k_step3d<S, C, PULL>, k_rho3d<S, C, PULL>,
     k_rho3f<S, C, PULL, IBC>, k_collide3f<S, C, PULL> (and k_psi3w, which every step runs),
     k_tile2d<S, C, TX, NT, OWN, WPE, PULL>, k_cptile<S, C, TX, NT, OWN, RPL, WPE, PULL>, and
     k_cp_march<S, C, W, OUT, PULL> of older databases."""
