@@ -1,10 +1,9 @@
 // Device-to-host copies into the caller's pageable memory.
 //
 // The runtime's own path copies a pageable destination chunk by chunk through one thread, which also
-// takes the page faults of a freshly allocated array: 13 GB/s measured for the 28.8 MB of a 1000 x 1200
-// field output, 10 GB/s for the 402 MB of a 4096^2 one, on a link that moves 53 GB/s.  Here the
-// device writes a ring of pinned chunks and a few threads, which live for the call alone, empty them into
-// the destination.
+// takes the page faults of a freshly allocated array: 17 GB/s measured into arrays in use, 10 GB/s into the fresh
+// 402 MB of a 4096^2 field output, on a link that moves 53 GB/s.  Here the device writes a ring of pinned
+// chunks and a few threads, which live for the call alone, empty them into the destination.
 #include <algorithm>
 #include <condition_variable>
 #include <cstring>
@@ -16,9 +15,10 @@
 namespace mcb {
 namespace {
 
-// Chunks of 2 MB and four threads: fields of 1000 x 1200 1.73 -> 1.02 ms into arrays in use, 2.2 -> 1.4 into
-// fresh ones, of 4096^2 39.9 -> 12.5 ms; chunks of 1 MB 14.2 ms (each costs about 15 us besides its transfer),
-// of 4 MB 11.1 but twice the pinned memory; two threads 17.9 ms, eight 12.1.
+// Chunks of 2 MB and four threads: fields of 1000 x 1200 (28.8 MB) 1.72 -> 0.99 ms into arrays in use, 2.8 -> 1.4
+// into fresh ones, of 4096^2 23.7 -> 10.7 and 39 -> 11.2; fresh ones of 4096^2 with chunks of 1 MB 14.2 ms
+// (each costs about 15 us besides its transfer), of 4 MB 11.1 but twice the pinned memory, with two
+// threads 17.9 ms, with eight 12.1, against 12.5 in the same run.
 constexpr int64_t CHUNK = int64_t(2) << 20;
 constexpr int WORKERS = 4;
 

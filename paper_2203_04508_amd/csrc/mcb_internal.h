@@ -174,7 +174,8 @@ hipError_t cp_wall_mu(mcb_ctx* c);                // chemical-potential model: m
 // step2d.hip / step3d.hip: one time step from the state (fcur, rcur) to (fnext, rnext), where r are
 // the boundary records of the state (pull = false: collision of fcur in place of the pull)
 hipError_t step_fused(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull);
-// tile2d.hip: the D2Q9 step where both lattices together hold at most TILE_BYTES
+// tile2d.hip: the D2Q9 step in FP64 and FP32 storage, of the pseudopotential model where both lattices together hold
+// at most TILE_BYTES, of the chemical-potential model at every size
 constexpr int64_t TILE_BYTES = 240000000;
 hipError_t tile2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, void* rnext, bool pull);
 // flat3d.hip: the D3Q19 step of FP64 and FP32 storage

@@ -334,8 +334,8 @@ hipError_t launch_w(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext,
     a.nsx = (a.nx + OUT - 1) / OUT;
     // segment height.  Wide strips: as many segments as the device holds in a number of resident
     // rounds -- four with FP32 storage (the shorter segments' extra halo rows cost less than the march
-    // loses when every workgroup moves in step with the others), one with FP16 storage, whose
-    // arithmetic is the limit and grows with the halo rows, and with FP64; one-wave strips (small
+    // loses when every workgroup moves in step with the others), one with FP16 storage (4096^2 272 us
+    // against 283 with four: the halo rows' arithmetic) and with FP64 (661 against 686); one-wave strips (small
     // lattices): enough workgroups to fill the chip several times over.
     int H;
     if (W == 64) {
@@ -963,9 +963,12 @@ hipError_t step2d(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, v
     // FP64 and FP32: the tile kernels re-read a ring around every tile, the march a few halo rows and
     // columns.  Where the two lattices stay in the 256 MB memory-side cache the ring costs little and
     // the tiles' shorter chains win (FP32 1800 x 1500, 194 MB: 43 us against 77; FP64 1531 x 1021,
-    // 225 MB: 47 against 81); past it the march does (FP32 2000 x 1850, 266 MB: 94 against 111;
-    // FP64 1400 x 1300, 262 MB: 88 against 84, 1800 x 1500, 389 MB: the same 125).  The chemical-
-    // potential model takes the tiles at every size.
+    // 225 MB: 47 against 81).  With FP32 the line is the cache: march 81 against tiles 84 at 246 MB (1900 x
+    // 1800), 93 against 111 at 266 (2000 x 1850).  FP64 moves twice the bytes for the same instructions and
+    // its tiles stay ahead for a while past it (march 91 against 85 at 262 MB, 1400 x 1300; 103 against
+    // 99 at 323; 125 both at 389, 1800 x 1500; 195 against 205 at 691; 642 against 717 at 4096^2): one line
+    // for both storages costs FP64 up to 7 % between 240 and 390 MB.  The chemical-potential model takes
+    // the tiles at every size.
     const bool cp = c->p.model == MCB_MODEL_CHEMPOT;
     if (c->p.precision != MCB_F16S && (cp || 2 * state_bytes(c->p.precision, 9, c->g.N) <= TILE_BYTES))
         return tile2d(c, fcur, rcur, fnext, rnext, pull);

@@ -6,7 +6,8 @@
 namespace mcb {
 namespace {
 
-// a buffer of at most BUF_MAX bytes (the boxes of this file are far below it)
+// a buffer of at most BUF_MAX bytes: mcb_create keeps a population lattice below it (the chemical-potential
+// model comes here up to that), mcb_build_links the boundary records
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t res32(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, int(bytes), 0x00020000);
 }
@@ -86,9 +87,9 @@ __device__ __forceinline__ void store_node(bool nt, __amdgpu_buffer_rsrc_t fb, _
 // Why tiles here: a march gives a workgroup one row at a time, a serial chain of about 2 us per row on
 // a box that leaves most of the chip idle; a tile runs its whole chain once (one round of loads,
 // then the loads that depend on the tags, and two barriers).  Time per step, one-wave row march against
-// tiles: 64^2 FP64 24.5 -> 4.4 us, 512^2 FP32 20.3 -> 8.0, 1024^2 FP32 32.6 -> 19.7 (3.8 TB/s of populations),
-// FP64 61.6 -> 31.9 (4.7 TB/s), 1531 x 1021 FP64 81 -> 45.  About 16 rounds of 550 vector instructions
-// per SIMD make up two thirds of the 1024^2 FP32 time.
+// tiles: 64^2 FP64 24.5 -> 4.1 us, 512^2 FP32 20.3 -> 8.0, 1024^2 FP32 32.6 -> 19.2 (3.9 TB/s of populations),
+// FP64 61.6 -> 32 (4.7 TB/s), 1531 x 1021 FP64 83 -> 47.  At 1024^2 FP32 the SIMDs issue vector
+// instructions in 72 % of their cycles, at six waves each.
 // Every node past the box's edge is its periodic image, so partial tiles need no cases of their own:
 // they only do not store.
 // WPE: waves per SIMD the registers are bounded to.
@@ -285,7 +286,7 @@ hipError_t tile_t(mcb_ctx* c, const void* fcur, const void* rcur, void* fnext, v
 //   5  force from both fields, eqs. 16-18 and the collision of the own nodes.
 // Measured against a march (one row per iteration, five barriers a row) that this replaces: 500 x 300
 // FP64 102 -> 11 us a step on a flat wall, 1024^2 FP32 on balls 144 -> 30, FP64 184 -> 55, 4096^2 FP32
-// 483 -> 435, FP64 1048 -> 847.  Vector instructions bound it on large boxes.
+// 483 -> 430, FP64 1048 -> 847.  At 4096^2 FP32 the SIMDs issue vector instructions in 71 % of their cycles.
 // Lanes t < OWN own the tile's nodes; where OWN < NT, ring entries go to the lanes past them first.
 template <class S, class C, int TX, int NT, int OWN, int RPL, int WPE, bool PULL, bool MRT>
 __global__ __launch_bounds__(NT, WPE) void k_cptile(ArgsCP<S, C> p) {
