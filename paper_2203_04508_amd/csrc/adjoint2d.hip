@@ -69,23 +69,32 @@ __device__ __forceinline__ void coefs(const AdjDev& A, const RC* __restrict__ la
 }
 
 // Links of a boundary node (tag tg > 0) on its pulled populations v (v[0] its own): v becomes the pre-collision
-// populations (eqs. 16-18).  The forcing terms are those of the stored state, in FP64: density and momentum
-// from the node's own populations, the force from its record (F = rho du; the collision left j + F).
+// populations (eqs. 16-18).  The forcing terms are those of the stored state, in FP64: an FP64 record holds them;
+// with an FP32 one density and momentum come from the node's own populations and only the force from
+// the record (F = rho du; the collision left j + F).
 template <class RC>
 __device__ __forceinline__ void links_on(const AdjDev& A, const RC* __restrict__ la, const RC* __restrict__ rec, int tg,
                                          double (&v)[9]) {
     RC h[RF2 + 8], a[Q2_LINKS];
     ld_vec(make_res(rec, uint64_t(A.nb) * REC2 * sizeof(RC)), uint32_t(tg >> 8) * uint32_t(REC2 * sizeof(RC)), h);
     coefs(A, la, tg, a);
-    double r = A.rho_ref + v[0], m[2] = {0, 0};
+    double kr = A.kF * double(h[0]), dx = double(h[1]), dy = double(h[2]), sx = double(h[3]), sy = double(h[4]);
+    double duu = double(h[5]);
+    if constexpr (sizeof(RC) == 4) {
+        double r = A.rho_ref + v[0], m[2] = {0, 0};
 #pragma unroll
-    for (int j = 1; j < 9; ++j) {
-        r += double(h[RF2 + j - 1]);
-        eadd(j, double(h[RF2 + j - 1]), m);
+        for (int j = 1; j < 9; ++j) {
+            r += double(h[RF2 + j - 1]);
+            eadd(j, double(h[RF2 + j - 1]), m);
+        }
+        const double ir = 1.0 / r, Fx = double(h[0]) * dx, Fy = double(h[0]) * dy;
+        kr = A.kF * r;
+        dx = Fx * ir;
+        dy = Fy * ir;
+        sx = 2.0 * (m[0] - Fx) * ir + dx;
+        sy = 2.0 * (m[1] - Fy) * ir + dy;
+        duu = 1.5 * (dx * sx + dy * sy);
     }
-    const double ir = 1.0 / r, Fx = double(h[0]) * double(h[1]), Fy = double(h[0]) * double(h[2]), kr = A.kF * r;
-    const double dx = Fx * ir, dy = Fy * ir, sx = 2.0 * (m[0] - Fx) * ir + dx, sy = 2.0 * (m[1] - Fy) * ir + dy;
-    const double duu = 1.5 * (dx * sx + dy * sy);
     double dm = 0.0;
     // a slot that a link replaces is never one that an eq. 16 link reads (its x2 = x - e_j is fluid)
 #pragma unroll

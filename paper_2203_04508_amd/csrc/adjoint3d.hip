@@ -101,26 +101,34 @@ __global__ __launch_bounds__(NT) void k_adj3_pre(Adj3 p, const S* __restrict__ g
             f[i] = kMixed<S> && i == 0 ? double(ldo(reinterpret_cast<const float*>(gt), q.node * 4u))
                                        : double(ldo(gt + plane_off<S>(i, N), nb[opp<1>(i)] * uint32_t(sizeof(S))));
         if (__any(tg > 0)) {
-            // eqs. 16-18.  The forcing terms are those of the stored state, in FP64: density and momentum from
-            // the node's own populations, the force from its record (F = rho du; the collision left j + F)
+            // eqs. 16-18.  The forcing terms are those of the stored state, in FP64: an FP64 record holds them;
+            // with an FP32 one density and momentum come from the node's own populations and only the
+            // force from the record (F = rho du; the collision left j + F)
             RC h[RF3 + 18];
             double a[18];
             ld_vec(make_res(rec, uint64_t(p.A.nb) * REC3 * sizeof(RC)),
                    tg > 0 ? uint32_t(tg - 1) * uint32_t(REC3 * sizeof(RC)) : OOB, h);
             coefs(la, p.A.nb, tg, a);
-            double own[19];
-            own[0] = f[0];
+            double kr = A.kF * double(h[0]), dx = double(h[1]), dy = double(h[2]), dz = double(h[3]);
+            double sx = double(h[4]), sy = double(h[5]), sz = double(h[6]), duu = double(h[7]);
+            if constexpr (sizeof(RC) == 4) {
+                double own[19], ro = A.rho_ref, m[3];
+                own[0] = f[0];
 #pragma unroll
-            for (int i = 1; i < 19; ++i) own[i] = double(h[RF3 + i - 1]);
-            double ro = A.rho_ref, m[3];
+                for (int i = 1; i < 19; ++i) own[i] = double(h[RF3 + i - 1]);
 #pragma unroll
-            for (int i = 0; i < 19; ++i) ro += own[i];
-            momentum(own, m);
-            const double ir = 1.0 / ro, kr = A.kF * ro, rr = double(h[0]);
-            const double Fx = rr * double(h[1]), Fy = rr * double(h[2]), Fz = rr * double(h[3]);
-            const double dx = Fx * ir, dy = Fy * ir, dz = Fz * ir;
-            const double sx = 2.0 * (m[0] - Fx) * ir + dx, sy = 2.0 * (m[1] - Fy) * ir + dy, sz = 2.0 * (m[2] - Fz) * ir + dz;
-            const double duu = 1.5 * (dx * sx + dy * sy + dz * sz);
+                for (int i = 0; i < 19; ++i) ro += own[i];
+                momentum(own, m);
+                const double ir = 1.0 / ro, Fx = double(h[0]) * dx, Fy = double(h[0]) * dy, Fz = double(h[0]) * dz;
+                kr = A.kF * ro;
+                dx = Fx * ir;
+                dy = Fy * ir;
+                dz = Fz * ir;
+                sx = 2.0 * (m[0] - Fx) * ir + dx;
+                sy = 2.0 * (m[1] - Fy) * ir + dy;
+                sz = 2.0 * (m[2] - Fz) * ir + dz;
+                duu = 1.5 * (dx * sx + dy * sy + dz * sz);
+            }
             double dm = 0.0;
             // a slot that a link replaces is never one that an eq. 16 link reads
 #pragma unroll
